@@ -134,7 +134,9 @@ static UpdWs plan_ws(const ModelDims& m, int32_t B, char* base) {
     return w;
 }
 
-int64_t update_workspace_bytes(const ModelDims& m, int32_t B) { return plan_ws(m, B, nullptr).bytes; }
+int64_t update_workspace_bytes(const ModelDims& m, int32_t B) {
+    return step_fused(m, B) ? step_workspace_bytes(m, B) : plan_ws(m, B, nullptr).bytes;
+}
 
 // ---------------------------------------------------------------------------
 // forward
@@ -1735,6 +1737,9 @@ hipError_t launch_update(const ModelDims& m, float* master, float* compute, cons
                          const float* inv_sigma, int32_t B, const float* feats, const float* ttft, float lr,
                          float* loss_out, float* grad_out, void* workspace, const DropArgs& drop, int n_cu,
                          hipStream_t s) {
+    if (step_fused(m, B))
+        return launch_step_fused(m, master, compute, mu, inv_sigma, B, {nullptr, feats, ttft, nullptr, nullptr}, lr,
+                                 {loss_out, nullptr, 0}, grad_out, workspace, drop, s);
     if (m.bf16)
         return run_update<true>(m, master, compute, mu, inv_sigma, B, feats, ttft, lr, loss_out, grad_out, workspace,
                                 drop, n_cu, s);

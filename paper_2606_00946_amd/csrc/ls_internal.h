@@ -325,6 +325,24 @@ hipError_t launch_admission(const float* a2, const float* t, const float* y_all,
 hipError_t launch_loss_accumulate(const float* loss, double* acc, int reset, hipStream_t s);
 hipError_t launch_loss_finish(const double* acc, int32_t count, float* out, hipStream_t s);
 
+// The step of a small batch in two launches (k_step.hip): rows from ax/ay, or
+// through codes as launch_gather_rows takes them; the step's loss to `step`,
+// and into a round's running sum (null: not wanted).
+struct StepRows {
+    const int32_t* code;
+    const float *ax, *ay, *bx, *by;
+};
+struct StepLoss {
+    float* step;
+    double* acc;
+    int reset;              // the sum starts with this step
+};
+bool step_fused(const ModelDims& m, int32_t B);
+int64_t step_workspace_bytes(const ModelDims& m, int32_t B);
+hipError_t launch_step_fused(const ModelDims& m, float* master, float* compute, const float* mu, const float* isig,
+                             int32_t B, const StepRows& rows, float lr, const StepLoss& loss, float* grad_out,
+                             void* workspace, const DropArgs& drop, hipStream_t s);
+
 // Online update.  Workspace layout is chosen by update_workspace_floats().
 int64_t update_workspace_bytes(const ModelDims& m, int32_t B);
 hipError_t launch_update(const ModelDims& m, float* master, float* compute, const float* mu,

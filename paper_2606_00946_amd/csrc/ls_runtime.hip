@@ -1360,15 +1360,24 @@ int ls_train_round(ls_ctx* c, int32_t epochs, int32_t batch, float lr, const int
         nb = 0;
         for (int32_t st = 0; st < n; st += batch) {
             const int32_t mb = n - st < batch ? n - st : batch;
-            LS_TIMED(c, K_UPDATE, s,
-                     ls::launch_gather_rows(dcodes + (int64_t)e * n + st, mb, d, bf.fifo_x, bf.fifo_y, bf.rep_x,
-                                            bf.rep_y, bx, by, s));
+            const int32_t* rows = dcodes + (int64_t)e * n + st;
+            const bool last = e + 1 == epochs && loss_out;
             const ls::DropArgs D = next_drop(c);
+            ++nb;
+            if (ls::step_fused(m, mb)) {
+                LS_TIMED(c, K_UPDATE, s,
+                         ls::launch_step_fused(m, TM.master, TM.compute, c->mu, c->isig, mb,
+                                               {rows, bf.fifo_x, bf.fifo_y, bf.rep_x, bf.rep_y}, lr,
+                                               {nullptr, last ? acc : nullptr, nb == 1}, nullptr, uws, D,
+                                               s));
+                continue;
+            }
+            LS_TIMED(c, K_UPDATE, s,
+                     ls::launch_gather_rows(rows, mb, d, bf.fifo_x, bf.fifo_y, bf.rep_x, bf.rep_y, bx, by, s));
             LS_TIMED(c, K_UPDATE, s,
                      ls::launch_update(m, TM.master, TM.compute, c->mu, c->isig, mb, bx, by, lr, step_loss, nullptr,
                                        uws, D, c->n_cu, s));
-            if (e + 1 == epochs && loss_out) LS_HIP(c, ls::launch_loss_accumulate(step_loss, acc, nb == 0, s));
-            ++nb;
+            if (last) LS_HIP(c, ls::launch_loss_accumulate(step_loss, acc, nb == 1, s));
         }
     }
     if (loss_out) LS_HIP(c, ls::launch_loss_finish(acc, nb, loss_out, s));

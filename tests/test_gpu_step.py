@@ -1,0 +1,46 @@
+"""The two-launch SGD step of small batches (Section 4.3.2) against the oracle,
+at the sizes where its tiling can go wrong: one sample, a workgroup's samples
+and one more, each switch of the samples per thread, the largest batch it takes
+and the first it does not; widths that do not fill a 16-wide weight tile, a
+16-input group or a thread group, unequal layers, and dropout.  The masters'
+compute copies, which the step writes itself, are checked by scoring with them:
+canonical scores of the updated weights, bit for bit."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle
+from gpu_helpers import GpuRun, note
+from paper_2606_00946_amd import synth
+from test_gpu_depth import compare_update, mode_of
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    (16, (64, 64), "fp32", [1, 4, 5, 1024, 1025, 3073]),
+    (37, (128, 128, 128), "fp32", [2, 3, 512, 513, 1537]),
+    (64, (256, 256), "bf16", [1, 256, 257, 769, 8192, 8193]),
+    (23, (96, 40), "bf16", [7, 33]),
+    (41, (17,), "fp32", [19, 256]),
+    (30, (100, 256, 33), "bf16", [5, 300]),
+]
+
+
+@pytest.mark.parametrize("d,hidden,dtype,B", [(d, h, t, b) for d, h, t, bs in CASES for b in bs])
+def test_step_parity(d, hidden, dtype, B):
+    note(f"step d={d} hidden={hidden} {dtype} B={B}")
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], d=d, hidden=hidden, dtype=dtype, update_batch=B + 8, R=33, N=5,
+                              seed=100 + B)
+    w = synth.generate(cfg)
+    feats, ttft = w.upd_feats[:B], w.upd_ttft[:B]
+    run = GpuRun(w)
+    run.ctx.ls_set_dropout(0.1, 5)
+    got = run.update(feats, ttft)
+    ref = oracle.update(mode_of(w), d, hidden, w.params, w.mu, w.inv_sigma, feats, ttft, w.lr, dropout=(0.1, 5, 0))
+    compare_update(w, got, ref, feats)
+    scored = run.score()
+    want = oracle.score(mode_of(w), d, hidden, got["params"], w.mu, w.inv_sigma, w.req_off, w.req_hashes, w.prompt_len,
+                        w.inst_feat, w.inst_off, w.inst_hashes)
+    assert np.array_equal(scored["scores"], want["scores"].astype(np.float32))
+    run.ctx.close()
