@@ -15,7 +15,9 @@
 // distances to the pool as it stands and among the chunk are computed up front
 // by a tiled kernel over the whole GPU, and one workgroup then walks the chunk,
 // taking each distance from the first table or, for a slot a candidate of the
-// chunk has taken, from the second.
+// chunk has taken, from the second.  This file decides for pools too large for
+// a thread's registers to hold its members (k_admit.hip decides for the rest),
+// with the per-slot state in memory.
 #include "ls_internal.h"
 
 namespace ls {
@@ -67,7 +69,6 @@ __global__ void embed_kernel(const float* __restrict__ a2, const float* __restri
 // Workgroup-wide lexicographic minimum of (value, index); index -1 = none.
 constexpr int kAdmitThreads = 1024;
 constexpr int32_t kAdmitChunk = 256;          // candidates whose distances are computed together
-constexpr int kLdsStateCap = 6144;            // largest pool whose per-slot state fits in LDS (144 KB)
 
 __device__ __forceinline__ void better_pair(double& v, int32_t& i, double ov, int32_t oi) {
     if (oi >= 0 && (i < 0 || ov < v || (ov == v && oi < i))) { v = ov; i = oi; }
@@ -90,55 +91,6 @@ __device__ __forceinline__ void block_min_pair(double& v, int32_t& i, double* sv
 
 // The pool keeps its pairwise distances D [cap x cap] (D[k][k] = +inf), so a
 // nearest neighbour is a row minimum.
-//
-// out[a * ldo + b] = emb_dist(A_a, B_b) for a < na, b < nb (+inf where a == b
-// when `diag`).  A workgroup computes a 16 x 64 tile; rows are staged through
-// LDS 32 units at a time and every thread keeps its four sums in registers, so
-// each distance is still summed over units in ascending order by one thread.
-constexpr int kDistA = 16, kDistB = 64, kDistJ = 32;
-
-__global__ __launch_bounds__(256) void dist_tile_kernel(const double* __restrict__ A, int32_t na,
-                                                        const double* __restrict__ B, int32_t nb, int H,
-                                                        double* __restrict__ out, int64_t ldo, int diag) {
-    __shared__ double sa[kDistA][kDistJ];
-    __shared__ double sb[kDistB][kDistJ + 1];
-    const int tid = threadIdx.x;
-    const int32_t a0 = (int32_t)blockIdx.y * kDistA, b0 = (int32_t)blockIdx.x * kDistB;
-    const int bl = tid & 63, ag = tid >> 6;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int j0 = 0; j0 < H; j0 += kDistJ) {
-        __syncthreads();
-        for (int x = tid; x < kDistA * kDistJ; x += 256) {
-            const int r = x / kDistJ, q = x - r * kDistJ;
-            const int32_t ar = a0 + r;
-            const int j = j0 + q;
-            sa[r][q] = (ar < na && j < H) ? A[(int64_t)ar * H + j] : 0.0;
-        }
-        for (int x = tid; x < kDistB * kDistJ; x += 256) {
-            const int r = x / kDistJ, q = x - r * kDistJ;
-            const int32_t br = b0 + r;
-            const int j = j0 + q;
-            sb[r][q] = (br < nb && j < H) ? B[(int64_t)br * H + j] : 0.0;
-        }
-        __syncthreads();
-        const int jn = H - j0 < kDistJ ? H - j0 : kDistJ;
-        for (int q = 0; q < jn; ++q) {
-            const double bv = sb[bl][q];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const double e = sa[4 * ag + u][q] - bv;
-                acc[u] += e * e;
-            }
-        }
-    }
-    const int32_t b = b0 + bl;
-    if (b >= nb) return;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int32_t ar = a0 + 4 * ag + u;
-        if (ar < na) out[(int64_t)ar * ldo + b] = (diag && ar == b) ? INFINITY : acc[u];
-    }
-}
 
 // minimum of row k of D over columns [0, n) other than k (lowest column on ties)
 __device__ __forceinline__ void row_min_block(const double* __restrict__ D, int32_t cap, int32_t n, int32_t k,
@@ -308,11 +260,7 @@ __device__ __forceinline__ int32_t admit_one(int32_t c, const double* __restrict
 // the member in slot k at the chunk's start, dcc[c][c'] (stride nch) its
 // distance to candidate c'.  origin[k] ends as the chunk-local index of the
 // last candidate that took slot k (-1: none), rslots / n_rslots as the list of
-// slots taken.  With CAPL > 0 (cap <= CAPL) the per-slot state -- nearest-
-// neighbour distances and slots, origins, the current candidate's distances --
-// lives in LDS for the whole chunk; otherwise in global memory (origin
-// cleared by the caller).
-template <int CAPL>
+// slots taken.  origin is cleared by the caller.
 __global__ __launch_bounds__(kAdmitThreads) void admit_chunk_kernel(
     const double* __restrict__ cemb, const float* __restrict__ cx, const float* __restrict__ cy, int d, int H,
     int32_t n, int32_t cap, int32_t nch, const double* __restrict__ dcp, const double* __restrict__ dcc,
@@ -320,26 +268,9 @@ __global__ __launch_bounds__(kAdmitThreads) void admit_chunk_kernel(
     float* __restrict__ ry, double* __restrict__ D, double* __restrict__ nnd, int32_t* __restrict__ nni,
     int32_t* __restrict__ redo, int32_t* __restrict__ admitted, int32_t* __restrict__ rslots,
     int32_t* __restrict__ n_rslots) {
-    constexpr bool kLds = CAPL > 0;
-    constexpr int L = kLds ? CAPL : 1;
     __shared__ double sv[8 * 16];
     __shared__ int32_t si[8 * 16];
     __shared__ int32_t n_redo;
-    __shared__ double l_nnd[L], l_row[L];
-    __shared__ int32_t l_nni[L], l_org[L];
-    double* nnd_w = kLds ? l_nnd : nnd;
-    double* row_w = kLds ? l_row : row;
-    int32_t* nni_w = kLds ? l_nni : nni;
-    int32_t* org_w = kLds ? l_org : origin;
-    if (kLds) {
-        for (int32_t k = threadIdx.x; k < cap; k += blockDim.x) {
-            l_org[k] = -1;
-            if (k < n) {
-                l_nnd[k] = nnd[k];
-                l_nni[k] = nni[k];
-            }
-        }
-    }
     if (threadIdx.x == 0) *n_rslots = 0;
     __syncthreads();
     for (int32_t c = 0; c < nch; ++c) {
@@ -349,27 +280,20 @@ __global__ __launch_bounds__(kAdmitThreads) void admit_chunk_kernel(
             for (int u = 0; u < 8; ++u) {            // clamped indices keep every load in bounds
                 const int32_t k = k0 + u * (int32_t)blockDim.x;
                 const int32_t kk = k < n ? k : n - 1;
-                const int32_t o = org_w[kk];
+                const int32_t o = origin[kk];
                 x[u] = o < 0 ? dcp[(int64_t)c * cap + kk] : dcc[(int64_t)c * nch + o];
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int32_t k = k0 + u * (int32_t)blockDim.x;
-                if (k < n) row_w[k] = x[u];
+                if (k < n) row[k] = x[u];
             }
         }
         __syncthreads();
-        (void)admit_one(c, cemb + (int64_t)c * H, cx + (int64_t)c * d, cy + c, d, H, n, cap, row_w, emb, rx, ry, D,
-                        nnd_w, nni_w, org_w, redo, admitted, rslots, n_rslots, sv, si, &n_redo);
+        (void)admit_one(c, cemb + (int64_t)c * H, cx + (int64_t)c * d, cy + c, d, H, n, cap, row, emb, rx, ry, D,
+                        nnd, nni, origin, redo, admitted, rslots, n_rslots, sv, si, &n_redo);
         if (n < cap) ++n;
         __syncthreads();
-    }
-    if (kLds) {
-        for (int32_t k = threadIdx.x; k < n; k += blockDim.x) {
-            nnd[k] = l_nnd[k];
-            nni[k] = l_nni[k];
-            origin[k] = l_org[k];
-        }
     }
 }
 
@@ -405,44 +329,59 @@ hipError_t launch_scatter_rows(const int32_t* dst, int32_t n, int d, const float
     return hipGetLastError();
 }
 
-int32_t admission_chunk(int32_t nc) { return nc < kAdmitChunk ? nc : kAdmitChunk; }
+namespace {
+
+int64_t up256(int64_t b) { return (b + 255) & ~int64_t(255); }
+
+}  // namespace
+
+int64_t admission_workspace_bytes(int32_t cap, int32_t nc) {
+    if (admission_walks(cap)) return admission_walk_bytes(cap, nc);
+    const int64_t ch = nc < kAdmitChunk ? nc : kAdmitChunk;
+    return up256((int64_t)cap * 4) * 3 + up256((int64_t)cap * 8) * 2 + up256(ch * cap * 8) + up256(ch * ch * 8) +
+           up256((ch + 1) * 4);
+}
 
 hipError_t launch_admission(const float* a2, const float* t, const float* y_all, int32_t n0, int32_t nc, int H, int d,
                             int32_t cap, const float* cx, const float* cy, double* cemb, double* emb, float* rx,
-                            float* ry, double* D, double* nnd, int32_t* nni, double* row, int32_t* redo,
-                            int32_t* admitted, double* dcp, double* dcc, int32_t* origin, int32_t* rslots,
-                            hipStream_t s) {
+                            float* ry, double* D, int32_t* admitted, void* workspace, hipStream_t s) {
     const int32_t n = n0 + nc;
     if (n <= 0 || cap <= 0) return hipSuccess;
     hipLaunchKernelGGL(embed_kernel, dim3(grid_of((int64_t)n * H, 256)), dim3(256), 0, s, a2, t, y_all, n, n0, H, emb,
                        cemb);
-    if (n0 > 0) {
-        hipLaunchKernelGGL(dist_tile_kernel, dim3(grid_of(n0, kDistB), grid_of(n0, kDistA)), dim3(256), 0, s, emb, n0,
-                           emb, n0, H, D, (int64_t)cap, 1);
-        hipLaunchKernelGGL(pool_nn_kernel, dim3((uint32_t)n0), dim3(256), 0, s, D, cap, n0, nnd, nni);
-    }
     hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t*>(admitted), 0u, 1, s);
     if (e != hipSuccess) return e;
-    const int32_t chunk = admission_chunk(nc);
+    if (admission_walks(cap))
+        return launch_admission_walk(n0, nc, H, d, cap, cx, cy, cemb, emb, rx, ry, D, admitted, workspace, s);
+    const int32_t chunk = nc < kAdmitChunk ? nc : kAdmitChunk;
+    char* w = reinterpret_cast<char*>(workspace);
+    auto take = [&](int64_t bytes) {
+        char* p = w;
+        w += up256(bytes);
+        return p;
+    };
+    int32_t* nni = reinterpret_cast<int32_t*>(take((int64_t)cap * 4));
+    int32_t* redo = reinterpret_cast<int32_t*>(take((int64_t)cap * 4));
+    int32_t* origin = reinterpret_cast<int32_t*>(take((int64_t)cap * 4));
+    double* nnd = reinterpret_cast<double*>(take((int64_t)cap * 8));
+    double* row = reinterpret_cast<double*>(take((int64_t)cap * 8));
+    double* dcp = reinterpret_cast<double*>(take((int64_t)chunk * cap * 8));
+    double* dcc = reinterpret_cast<double*>(take((int64_t)chunk * chunk * 8));
+    int32_t* rslots = reinterpret_cast<int32_t*>(take(((int64_t)chunk + 1) * 4));
+    if (n0 > 0) {
+        launch_distances(emb, n0, emb, n0, H, D, cap, true, s);
+        hipLaunchKernelGGL(pool_nn_kernel, dim3((uint32_t)n0), dim3(256), 0, s, D, cap, n0, nnd, nni);
+    }
     int32_t size = n0;
     for (int32_t c0 = 0; c0 < nc; c0 += chunk) {
         const int32_t nch = nc - c0 < chunk ? nc - c0 : chunk;
         const double* ce = cemb + (int64_t)c0 * H;
-        if (size > 0)
-            hipLaunchKernelGGL(dist_tile_kernel, dim3(grid_of(size, kDistB), grid_of(nch, kDistA)), dim3(256), 0, s, ce,
-                               nch, emb, size, H, dcp, (int64_t)cap, 0);
-        hipLaunchKernelGGL(dist_tile_kernel, dim3(grid_of(nch, kDistB), grid_of(nch, kDistA)), dim3(256), 0, s, ce, nch,
-                           ce, nch, H, dcc, (int64_t)nch, 0);
-        if (cap <= kLdsStateCap) {
-            hipLaunchKernelGGL(admit_chunk_kernel<kLdsStateCap>, dim3(1), dim3(kAdmitThreads), 0, s, ce,
-                               cx + (int64_t)c0 * d, cy + c0, d, H, size, cap, nch, dcp, dcc, origin, row, emb, rx, ry,
-                               D, nnd, nni, redo, admitted, rslots, rslots + chunk);
-        } else {
-            if ((e = launch_fill_u32(reinterpret_cast<uint32_t*>(origin), 0xffffffffu, cap, s)) != hipSuccess) return e;
-            hipLaunchKernelGGL(admit_chunk_kernel<0>, dim3(1), dim3(kAdmitThreads), 0, s, ce, cx + (int64_t)c0 * d,
-                               cy + c0, d, H, size, cap, nch, dcp, dcc, origin, row, emb, rx, ry, D, nnd, nni, redo,
-                               admitted, rslots, rslots + chunk);
-        }
+        launch_distances(ce, nch, emb, size, H, dcp, cap, false, s);
+        launch_distances(ce, nch, ce, nch, H, dcc, nch, true, s);
+        if ((e = launch_fill_u32(reinterpret_cast<uint32_t*>(origin), 0xffffffffu, cap, s)) != hipSuccess) return e;
+        hipLaunchKernelGGL(admit_chunk_kernel, dim3(1), dim3(kAdmitThreads), 0, s, ce, cx + (int64_t)c0 * d, cy + c0, d,
+                           H, size, cap, nch, dcp, dcc, origin, row, emb, rx, ry, D, nnd, nni, redo, admitted, rslots,
+                           rslots + chunk);
         size = size + nch < cap ? size + nch : cap;
         if (c0 + nch < nc)                           // the last chunk's columns are never read
             hipLaunchKernelGGL(flush_columns_kernel, dim3(grid_of(size, 256), (uint32_t)nch), dim3(256), 0, s, rslots,

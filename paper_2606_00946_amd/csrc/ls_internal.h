@@ -317,11 +317,20 @@ hipError_t launch_scatter_rows(const int32_t* dst, int32_t n, int d, const float
 // chunk x cap distances, dcc chunk x chunk, origin cap slots, row and redo cap,
 // rslots chunk + 1.
 int32_t admission_chunk(int32_t nc);
+// Candidates against the pool: embeddings, decisions, the pool's new rows
+// (k_buffer.hip; pools whose members fit a workgroup's registers in
+// k_admit.hip).
 hipError_t launch_admission(const float* a2, const float* t, const float* y_all, int32_t n0, int32_t nc, int H, int d,
                             int32_t cap, const float* cx, const float* cy, double* cemb, double* emb, float* rx,
-                            float* ry, double* D, double* nnd, int32_t* nni, double* row, int32_t* redo,
-                            int32_t* admitted, double* dcp, double* dcc, int32_t* origin, int32_t* rslots,
-                            hipStream_t s);
+                            float* ry, double* D, int32_t* admitted, void* workspace, hipStream_t s);
+int64_t admission_workspace_bytes(int32_t cap, int32_t nc);
+bool admission_walks(int32_t cap);
+int64_t admission_walk_bytes(int32_t cap, int32_t nc);
+hipError_t launch_admission_walk(int32_t n0, int32_t nc, int H, int d, int32_t cap, const float* cx, const float* cy,
+                                 const double* cemb, double* emb, float* rx, float* ry, double* D, int32_t* admitted,
+                                 void* workspace, hipStream_t s);
+void launch_distances(const double* A, int32_t na, const double* B, int32_t nb, int H, double* out, int64_t ldo,
+                      bool sym, hipStream_t s);
 hipError_t launch_loss_accumulate(const float* loss, double* acc, int reset, hipStream_t s);
 hipError_t launch_loss_finish(const double* acc, int32_t count, float* out, hipStream_t s);
 

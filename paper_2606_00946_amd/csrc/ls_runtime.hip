@@ -86,8 +86,7 @@ struct ls_ctx {
     struct Buffer {
         int32_t fifo_cap = 0, rep_cap = 0, fifo_count = 0, fifo_head = 0, rep_count = 0;
         float *fifo_x = nullptr, *fifo_y = nullptr, *rep_x = nullptr, *rep_y = nullptr;
-        double *emb = nullptr, *nnd = nullptr, *D = nullptr;   // D: pairwise distances [rep_cap x rep_cap]
-        int32_t* nni = nullptr;
+        double *emb = nullptr, *D = nullptr;   // D: pairwise distances [rep_cap x rep_cap]
         void* ws = nullptr;
         size_t ws_cap = 0;
     } buf;
@@ -483,7 +482,7 @@ void ls_destroy(ls_ctx* c) {
                         (void*)c->frag32, (void*)c->tables.keys, c->fpb,
                         (void*)c->inst_meta, (void*)c->tables.flags, c->tws, c->ws, (void*)c->buf.fifo_x,
                         (void*)c->buf.fifo_y, (void*)c->buf.rep_x, (void*)c->buf.rep_y, (void*)c->buf.emb,
-                        (void*)c->buf.nnd, (void*)c->buf.nni, (void*)c->buf.D, c->buf.ws, (void*)c->idx.hash,
+                        (void*)c->buf.D, c->buf.ws, (void*)c->idx.hash,
                         (void*)c->idx.stamp, (void*)c->idx.hash2, (void*)c->idx.stamp2, (void*)c->idx.entry_of,
                         (void*)c->idx.small, c->idx.ws, (void*)c->sh_master, (void*)c->sh_compute, c->upd_ws,
                         (void*)c->sh_frag16, (void*)c->sh_frag32})
@@ -1137,12 +1136,10 @@ int ls_buffer_init(ls_ctx* c, int32_t fifo_cap, int32_t replay_cap) {
     if (!dev.ok) return fail(c, LS_ERR_DEVICE, "cannot select device %d", c->device);
     LS_HIP(c, hipDeviceSynchronize());
     ls_ctx::Buffer& B = c->buf;
-    for (void* p : {(void*)B.fifo_x, (void*)B.fifo_y, (void*)B.rep_x, (void*)B.rep_y, (void*)B.emb, (void*)B.nnd,
-                    (void*)B.nni, (void*)B.D})
+    for (void* p : {(void*)B.fifo_x, (void*)B.fifo_y, (void*)B.rep_x, (void*)B.rep_y, (void*)B.emb, (void*)B.D})
         if (p) LS_HIP(c, hipFree(p));
     B.fifo_x = B.fifo_y = B.rep_x = B.rep_y = nullptr;
-    B.emb = B.nnd = B.D = nullptr;
-    B.nni = nullptr;
+    B.emb = B.D = nullptr;
     B.fifo_cap = B.rep_cap = B.fifo_count = B.fifo_head = B.rep_count = 0;
     const int d = c->dims.d, H = c->dims.hl;
     const int32_t rc1 = replay_cap > 0 ? replay_cap : 1;
@@ -1151,8 +1148,6 @@ int ls_buffer_init(ls_ctx* c, int32_t fifo_cap, int32_t replay_cap) {
               hipMalloc((void**)&B.rep_x, sizeof(float) * (size_t)rc1 * d) == hipSuccess &&
               hipMalloc((void**)&B.rep_y, sizeof(float) * (size_t)rc1) == hipSuccess &&
               hipMalloc((void**)&B.emb, sizeof(double) * (size_t)rc1 * H) == hipSuccess &&
-              hipMalloc((void**)&B.nnd, sizeof(double) * (size_t)rc1) == hipSuccess &&
-              hipMalloc((void**)&B.nni, sizeof(int32_t) * (size_t)rc1) == hipSuccess &&
               hipMalloc((void**)&B.D, sizeof(double) * (size_t)rc1 * rc1) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
@@ -1212,18 +1207,13 @@ int ls_buffer_push(ls_ctx* c, int32_t B, const float* feats, const float* ttft, 
     const int32_t n_all = bf.rep_cap > 0 ? n0 + nc : 0;
     // workspace
     const int64_t f_fwd = n_all > 0 ? ls::forward_rows_floats(m, n_all) : 0;
-    const int64_t ch = nc > 0 ? ls::admission_chunk(nc) : 1;
-    const int64_t rcap = bf.rep_cap > 0 ? bf.rep_cap : 1;
+    const int64_t adm_bytes = n_all > 0 && nc > 0 ? ls::admission_workspace_bytes(bf.rep_cap, nc) : 0;
     size_t need = (size_t)round_up((int64_t)(nc + B) * 4, 256)                       // codes
-                  + (size_t)round_up((int64_t)(nc > 0 ? nc : 1) * (d + 1) * 4, 256)     // candidate rows
-                  + (size_t)round_up((int64_t)(n_all > 0 ? n_all : 1) * (d + 1) * 4, 256)  // forward input
+                  + (size_t)round_up((int64_t)(nc > 0 ? nc : 1) * (d + 1) * 4, 256) + 256     // candidate rows
+                  + (size_t)round_up((int64_t)(n_all > 0 ? n_all : 1) * (d + 1) * 4, 256) + 256  // forward input
                   + (size_t)round_up(f_fwd * 4, 256)
                   + (size_t)round_up((int64_t)(nc > 0 ? nc : 1) * H * 8, 256)          // candidate embeddings
-                  + (size_t)round_up((int64_t)(bf.rep_cap > 0 ? bf.rep_cap : 1) * 4, 256) + 256
-                  + (size_t)round_up((int64_t)(bf.rep_cap > 0 ? bf.rep_cap : 1) * 8, 256)           // distance row
-                  + (size_t)round_up(ch * rcap * 8, 256) + (size_t)round_up(ch * ch * 8, 256)     // chunk distances
-                  + (size_t)round_up(rcap * 4, 256)                                              // slot origins
-                  + (size_t)round_up((ch + 1) * 4, 256);                                         // slots taken
+                  + 512 + (size_t)round_up(adm_bytes, 256);                            // the admission's scratch
     int rc = grow(c, &bf.ws, &bf.ws_cap, need, s);
     if (rc) return rc;
     WsCarve w{(char*)bf.ws};
@@ -1234,13 +1224,8 @@ int ls_buffer_push(ls_ctx* c, int32_t B, const float* feats, const float* ttft, 
     float* ay = w.take<float>(n_all > 0 ? n_all : 1);
     float* fws = w.take<float>(f_fwd > 0 ? f_fwd : 1);
     double* cemb = w.take<double>((int64_t)(nc > 0 ? nc : 1) * H);
-    int32_t* redo = w.take<int32_t>(bf.rep_cap > 0 ? bf.rep_cap : 1);
     int32_t* adm = w.take<int32_t>(64);
-    double* drow = w.take<double>(bf.rep_cap > 0 ? bf.rep_cap : 1);
-    double* dcp = w.take<double>(ch * rcap);
-    double* dcc = w.take<double>(ch * ch);
-    int32_t* origin = w.take<int32_t>(rcap);
-    int32_t* rslots = w.take<int32_t>(ch + 1);
+    char* adm_ws = w.take<char>(adm_bytes);
     // stage the codes
     rc = stage_reserve(c, sizeof(int32_t) * (size_t)(nc + B) + 64);
     if (rc) return rc;
@@ -1263,8 +1248,7 @@ int ls_buffer_push(ls_ctx* c, int32_t B, const float* feats, const float* ttft, 
                  ls::launch_forward_rows(m, train_model(c).compute, c->mu, c->isig, n_all, ax, fws, &a2, &t, s));
         LS_TIMED(c, K_BUFFER, s,
                  ls::launch_admission(a2, t, ay, n0, nc, H, d, bf.rep_cap, cx, cy, cemb, bf.emb, bf.rep_x, bf.rep_y,
-                                      bf.D, bf.nnd, bf.nni, drow, redo, admitted ? admitted : adm, dcp, dcc,
-                                      origin, rslots, s));
+                                      bf.D, admitted ? admitted : adm, adm_ws, s));
     } else if (admitted) {
         LS_TIMED(c, K_BUFFER, s, ls::launch_fill_u32(reinterpret_cast<uint32_t*>(admitted), 0u, 1, s));
     }
