@@ -844,9 +844,11 @@ __global__ __launch_bounds__(kResolveThreads) void followers_resolve_kernel(
     if (threadIdx.x == 0) n_list[blockIdx.x] = lcount;
 }
 
-// Block b probes the pairs of slice b, 16 per wave (four lanes per bucket),
+// Blocks (b, *) probe the pairs of slice b, 16 per wave (four lanes per bucket),
 // walking from the common prefix, or with prefix-closed caches (`closed`)
-// galloping from it.
+// galloping from it.  A wave's pairs cost a chain of about five dependent reads,
+// mostly to find block c missing, so what counts is that few waves take a second
+// set: the slice's list is dealt to gridDim.y blocks.
 __global__ __launch_bounds__(256) void followers_probe_kernel(ProbeTables T, int32_t N, int64_t chunk,
                                                               const int64_t* __restrict__ req_off,
                                                               const uint64_t* __restrict__ req_hashes,
@@ -858,7 +860,8 @@ __global__ __launch_bounds__(256) void followers_probe_kernel(ProbeTables T, int
     const int group = lane >> 2, q = lane & 3, shift = group * 4;
     const int64_t total = n_list[blockIdx.x];
     const int64_t* __restrict__ mine = list + (int64_t)blockIdx.x * chunk;
-    for (int64_t w = threadIdx.x >> 6; w * 16 < total; w += blockDim.x >> 6) {
+    const int64_t waves = (int64_t)gridDim.y * (blockDim.x >> 6);
+    for (int64_t w = (int64_t)blockIdx.y * (blockDim.x >> 6) + (threadIdx.x >> 6); w * 16 < total; w += waves) {
         const int64_t idx = w * 16 + group;
         if (idx >= total) continue;                      // whole group of 4 lanes skips together
         const int64_t pair = mine[idx];
@@ -984,8 +987,12 @@ hipError_t launch_prefix_match(const CacheTables& t, int32_t R, int32_t N, const
         hipLaunchKernelGGL(followers_resolve_kernel<false>, dim3((uint32_t)slices), dim3(kResolveThreads), 0, s, R, N,
                            chunk, lead_of, lcp_of, cont_of, qseen, reinterpret_cast<const uint4*>(qinst), qall, overlap, list,
                            n_list);
-    hipLaunchKernelGGL(followers_probe_kernel, dim3((uint32_t)slices), dim3(256), 0, s, T, N, chunk, req_off,
-                       req_hashes, lcp_of, list, n_list, overlap, closed ? 1 : 0);
+    // blocks per slice: about 16 a CU in all, and no more than take the whole slice at once (64 pairs each)
+    int64_t split = (int64_t)n_cu * 16 / slices;
+    if (split > (chunk + 63) / 64) split = (chunk + 63) / 64;
+    if (split < 1) split = 1;
+    hipLaunchKernelGGL(followers_probe_kernel, dim3((uint32_t)slices, (uint32_t)split), dim3(256), 0, s, T, N, chunk,
+                       req_off, req_hashes, lcp_of, list, n_list, overlap, closed ? 1 : 0);
     return hipGetLastError();
 }
 
