@@ -374,8 +374,11 @@ __device__ __forceinline__ CandView cand_view(const IndexCommit& C, int32_t i) {
     return V;
 }
 
-// One selection pass (digit `shift / 8`): histogram of the digit over each
-// selecting instance's candidates that match its prefix so far.
+// One selection pass (the eight bits from `shift` up): histogram of the digit
+// over each selecting instance's candidates that match its prefix so far.  Lanes
+// that add to one LDS word take turns, and a digit above the stamps' varying bits
+// is the same for all: a wave whose matching lanes agree adds once (a pass over
+// 6.4 M candidates 35.3 -> 26.5 us on average).
 __global__ __launch_bounds__(256) void select_hist_kernel(IndexCommit C, int shift) {
     __shared__ uint32_t lh[256];
     const int64_t nchunks = C.chunk0[C.N];
@@ -400,8 +403,19 @@ __global__ __launch_bounds__(256) void select_hist_kernel(IndexCommit C, int shi
             ok[u] = v < v1 && V.get(v, h, st[u]);
         }
 #pragma unroll
-        for (int u = 0; u < kPer; ++u)
-            if (ok[u] && (st[u] & mask) == prefix) atomicAdd(&lh[(st[u] >> shift) & 255u], 1u);
+        for (int u = 0; u < kPer; ++u) {
+            const bool in = ok[u] && (st[u] & mask) == prefix;
+            const uint32_t digit = (uint32_t)(st[u] >> shift) & 255u;
+            const uint64_t m = __ballot(in);
+            if (m == 0) continue;
+            const int first = __ffsll((long long)m) - 1;
+            const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)digit, first);
+            if (__ballot(in && digit == d0) == m) {
+                if ((int)(threadIdx.x & 63) == first) atomicAdd(&lh[d0], (uint32_t)__popcll(m));
+            } else if (in) {
+                atomicAdd(&lh[digit], 1u);
+            }
+        }
         __syncthreads();
         if (lh[threadIdx.x]) atomicAdd(&C.sel_hist[(int64_t)i * 256 + threadIdx.x], lh[threadIdx.x]);
         __syncthreads();
@@ -653,12 +667,16 @@ hipError_t launch_commit(const CacheTables& T, const IndexCommit& C, hipStream_t
     hipLaunchKernelGGL(commit_plan_kernel, dim3(1), dim3(1024), 0, s, C);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const int grid = grid_of(C.chunk_bound * 256, 256, C.n_cu);
-    for (int p = 7; p >= 0; --p) {
-        hipLaunchKernelGGL(select_hist_kernel, dim3(grid), dim3(256), 0, s, C, 8 * p);
+    // No stamp has a bit above this epoch's (loaded entries': below 2^32): six or seven digits for
+    // the first 2^12 commits, eight after.  The last digit may reach into bits already selected; its candidates agree there.
+    int shift = kStampKBits + kStampRBits + 32 - __builtin_clz(C.epoch | 1u);
+    do {
+        shift = shift > 8 ? shift - 8 : 0;
+        hipLaunchKernelGGL(select_hist_kernel, dim3(grid), dim3(256), 0, s, C, shift);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(select_digit_kernel, dim3((uint32_t)((N + 3) / 4)), dim3(256), 0, s, C, 8 * p);
+        hipLaunchKernelGGL(select_digit_kernel, dim3((uint32_t)((N + 3) / 4)), dim3(256), 0, s, C, shift);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
+    } while (shift > 0);
     hipLaunchKernelGGL(select_compact_multi_kernel, dim3(grid), dim3(256), 0, s, C);
     return hipGetLastError();
 }
