@@ -45,6 +45,7 @@ struct StepArgs {
     int L, d, B, hl;
     StepLayer layer[4];                       // the hidden layers, then the head
     int64_t c_w1;                             // row-major first layer of two-layer compute copies, or -1
+    int n_master, n_compute;                  // floats
     const float* mu;
     const float* isig;
     float* master;
@@ -139,6 +140,17 @@ __global__ __launch_bounds__(kStepThreads) void step_rows_kernel(StepArgs P) {
     __shared__ float gs[S], w3[kStepWidth];
     const int tid = (int)threadIdx.x, unit = tid % W, grp = tid / W;
     const int64_t b0 = (int64_t)blockIdx.x * S;
+    // Every XCD's L2 starts a step without the weights, which the last step's tiles left in memory: a workgroup reads
+    // one word of each 128-byte line of its share of them, an eighth of the workgroups (consecutive ones go to
+    // different XCDs) taking all (25.1 -> 24.0 us a step at B = 256 of 3 x 128, 29.9 -> 29.1 at 1,000).
+    uint32_t touched = 0;
+    {
+        const int share = (int)(gridDim.x + 7) / 8, mine = (int)blockIdx.x / 8;
+        const int lc = (P.n_compute + 31) / 32, lines = lc + (P.n_master + 31) / 32;
+#pragma unroll 4
+        for (int q = mine * kStepThreads + tid; q < lines; q += share * kStepThreads)
+            touched |= __float_as_uint(q < lc ? P.compute[32 * q] : P.master[32 * (q - lc)]);
+    }
     for (int e = tid; e < S * P.d; e += kStepThreads) {
         const int i = e / P.d, c = e - i * P.d;
         const int64_t b = b0 + i;
@@ -153,6 +165,7 @@ __global__ __launch_bounds__(kStepThreads) void step_rows_kernel(StepArgs P) {
         xs[0][i * kStepRow + c] = v;
     }
     for (int k = tid; k < P.hl; k += kStepThreads) w3[k] = P.compute[P.layer[P.L].wt + k];
+    asm volatile("" ::"v"(touched));
     __syncthreads();
     // forward; bit i of mask[l]: this thread's unit of sample i is on (z > 0)
     uint32_t mask[3] = {0u, 0u, 0u};
@@ -395,6 +408,8 @@ hipError_t launch_step_fused(const ModelDims& m, float* master, float* compute, 
         if (l < m.L) { Y.a = take((int64_t)Y.out * B); Y.dl = take((int64_t)Y.out * B); }
     }
     P.c_w1 = m.L == 2 ? m.c_w1 : -1;
+    P.n_master = (int)m.n_params;
+    P.n_compute = (int)m.n_compute;
     P.mu = mu; P.isig = isig; P.master = master; P.compute = compute;
     P.code = rows.code; P.ax = rows.ax; P.ay = rows.ay; P.bx = rows.bx; P.by = rows.by;
     P.xn = take((int64_t)m.d * B);
