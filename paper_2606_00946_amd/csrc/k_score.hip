@@ -122,7 +122,8 @@ hipError_t launch_refresh_compute_copy(const ModelDims& m, const float* master, 
 constexpr int kPartInsts = 8;
 constexpr int kPartCols = 256;
 
-template <bool BF>
+// TR: w1 is W1^T [d][h1] (one and three layers), else W1 [h1][d].
+template <bool BF, bool TR>
 __global__ __launch_bounds__(256) void instance_partial_kernel(const float* __restrict__ w1,
                                                                const float* __restrict__ b1,
                                                                const float* __restrict__ mu,
@@ -135,7 +136,8 @@ __global__ __launch_bounds__(256) void instance_partial_kernel(const float* __re
     for (int kb = 0; kb < h1; kb += 256) {                        // uniform
         const int k = kb + tid;
         const bool kval = k < h1;
-        const float* __restrict__ w = w1 + (int64_t)(kval ? k : 0) * d;
+        const float* __restrict__ w = w1 + (int64_t)(kval ? k : 0) * (TR ? 1 : d);
+        const int64_t step = TR ? h1 : 1;                         // from one column to the next
         float acc[kPartInsts];
         const float bk = kval ? b1[k] : 0.0f;
 #pragma unroll
@@ -158,14 +160,14 @@ __global__ __launch_bounds__(256) void instance_partial_kernel(const float* __re
             for (; c + 8 <= nc; c += 8) {
                 float wc[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) wc[j] = w[c0 + c + j];
+                for (int j = 0; j < 8; ++j) wc[j] = w[(c0 + c + j) * step];
 #pragma unroll
                 for (int j = 0; j < 8; ++j)
 #pragma unroll
                     for (int ii = 0; ii < kPartInsts; ++ii) acc[ii] = __builtin_fmaf(wc[j], xs[ii][c + j], acc[ii]);
             }
             for (; c < nc; ++c) {
-                const float wc = w[c0 + c];
+                const float wc = w[(c0 + c) * step];
 #pragma unroll
                 for (int ii = 0; ii < kPartInsts; ++ii) acc[ii] = __builtin_fmaf(wc, xs[ii][c], acc[ii]);
             }
@@ -183,12 +185,12 @@ hipError_t launch_instance_partial(const ModelDims& m, const float* compute, con
                                    hipStream_t s) {
     const int64_t grid = ((int64_t)N + kPartInsts - 1) / kPartInsts;
     if (grid == 0) return hipSuccess;
-    if (m.bf16)
-        hipLaunchKernelGGL(instance_partial_kernel<true>, dim3((uint32_t)grid), dim3(256), 0, s, compute + m.c_w1,
-                           compute + m.c_b1, mu, inv_sigma, inst_feat, m.d, m.d_inst, m.h1, N, part_t);
-    else
-        hipLaunchKernelGGL(instance_partial_kernel<false>, dim3((uint32_t)grid), dim3(256), 0, s, compute + m.c_w1,
-                           compute + m.c_b1, mu, inv_sigma, inst_feat, m.d, m.d_inst, m.h1, N, part_t);
+    auto launch = [&](auto* kernel, const float* w1) {
+        hipLaunchKernelGGL(kernel, dim3((uint32_t)grid), dim3(256), 0, s, w1, compute + m.c_bl[0], mu, inv_sigma,
+                           inst_feat, m.d, m.d_inst, m.h[0], N, part_t);
+    };
+    if (m.L == 2) launch(m.bf16 ? instance_partial_kernel<true, false> : instance_partial_kernel<false, false>, compute + m.c_w1);
+    else launch(m.bf16 ? instance_partial_kernel<true, true> : instance_partial_kernel<false, true>, compute + m.c_wt[0]);
     return hipGetLastError();
 }
 

@@ -821,8 +821,9 @@ int run_pipeline(ls_ctx* c, WsCarve& w, int32_t R, int32_t N, const int64_t* req
                                                          c->prefix_join),
                                      c->prefix_closed, s));
     const uint8_t* band = nullptr;
-    if (layer_by_layer(m)) {
-        // other depths: the pairs' rows through the layer-by-layer canonical forward
+    const bool chain = m.mfma_chains && ls::chain_mfma_supported(m);
+    if (layer_by_layer(m) && !chain) {
+        // other depths and unequal widths: the pairs' rows through the layer-by-layer canonical forward
         float* gws = w.take<float>(ls::generic_score_floats(m, pairs));
         if (!w.ok()) return fail(c, LS_ERR_NOMEM, "%s", undersized);
         LS_TIMED(c, K_SCORE, s,
@@ -861,7 +862,7 @@ int run_pipeline(ls_ctx* c, WsCarve& w, int32_t R, int32_t N, const int64_t* req
                       ls::launch_rescore(m, c->compute, c->mu, c->isig, part_t, R, N, req_off, prompt_len, ov, list,
                                          count + 32, sc, c->n_cu, s));
         band = flags;
-    } else if (m.mfma_chains && ls::chain_mfma_supported(m)) {
+    } else if (chain) {
         LS_TIMED_NEXT(c, K_SCORE, s,
                       ls::launch_score_chain_mfma(m, c->compute, c->mu, c->isig, part_t, R, N, req_off, prompt_len, ov,
                                                   nullptr, nullptr, c->n_cu, sc, s));
