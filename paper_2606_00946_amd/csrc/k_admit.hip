@@ -19,7 +19,8 @@
 // What bounds the walk is latency: three barriers and one round of dependent
 // global reads per admission.  A push of 1,000 rows into full pools of 5,000
 // (256 units): 14.8 ms when one workgroup searched whole rows with its state in
-// LDS, 1.27 ms now (2.8 us per admission, most of it in the walk).
+// LDS, 1.28 ms now; the first push of 1,000 on new rows, 903 of them admitted,
+// 34.7 and 9.0 ms (12.2 when one wave searched a whole row by itself).
 //
 // Distances are compared as the bit patterns of non-negative doubles, which
 // order like the numbers; a NaN's pattern is above infinity's, so it is never
@@ -36,6 +37,7 @@ constexpr int kWalkOwn = 6;                            // members per thread
 constexpr int kWalkSlots = kWalkThreads * kWalkOwn;    // 6,144
 constexpr int kWalkChunk = 512;                        // candidates decided per launch
 constexpr int kWalkLook = 8;                           // candidates whose distance is found ahead
+constexpr int kWalkFull = 8;                           // whole rows searched between two barriers
 constexpr int kTop = 12;                               // entries of a point's list
 constexpr uint64_t kInfBits = 0x7ff0000000000000ull;
 constexpr uint64_t kNoBits = ~0ull;                    // no value
@@ -202,8 +204,8 @@ __device__ __forceinline__ void lds_barrier() {
 // out), the rest the candidates (row of dcp).  Ties in any order: only the
 // values decide.  A thread offers the two nearest of its 24, so a round is one
 // reduction; a list ends (-2: more may follow, -1: nothing does) when a thread
-// has given both, and the walk then reads the whole row in the rare case that
-// none of the entries is a member any more.  5,512 points: 49 us (151 with every
+// has given both, and the walk then searches the whole row, all waves a part each,
+// when none of the entries is a member any more.  5,512 points: 49 us (151 with every
 // thread offering all of its own).
 // ---------------------------------------------------------------------------
 constexpr int kTopThreads = 256;
@@ -298,7 +300,10 @@ __global__ __launch_bounds__(kWalkThreads) void walk_kernel(WalkArgs W) {
     __shared__ uint64_t near[kWalkChunk];              // this candidate's distances to the chunk's
     __shared__ uint64_t look_d[kWalkLook], wmin_v[kWalkThreads / 64];
     __shared__ int32_t wmin_s[kWalkThreads / 64];
-    __shared__ int32_t n_redo;
+    __shared__ int32_t n_redo, n_full;
+    __shared__ int32_t full[kWalkSlots + 1 + kWalkLook];   // points whose list holds no member any more
+    __shared__ uint64_t part_v[kWalkFull][kWalkThreads / 64];
+    __shared__ int32_t part_s[kWalkFull][kWalkThreads / 64];
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t n0 = W.n, cap = W.cap, nch = W.nch;
@@ -327,7 +332,7 @@ __global__ __launch_bounds__(kWalkThreads) void walk_kernel(WalkArgs W) {
         org[k] = -1;
     }
     if (tid < kWalkChunk) slot_of[tid] = -1;
-    if (tid == 0) n_redo = 0;
+    if (tid == 0) n_redo = n_full = 0;
     // the pool's smallest nearest-neighbour distance, lowest slot on ties
     uint64_t pool_v = kNoBits;
     int32_t pool_s = -1;
@@ -355,7 +360,8 @@ __global__ __launch_bounds__(kWalkThreads) void walk_kernel(WalkArgs W) {
     };
     // nearest member of one point, by one wave: value and slot, kNoBits and -1 without any.
     // `a` >= 0: candidate a, else the member that slot k started with.
-    auto nearest = [&](int32_t k, int32_t a, int32_t upto, uint64_t& bv, int32_t& bs) {
+    // Returns whether the whole row is wanted too: every listed member has been replaced and there may be others.
+    auto nearest = [&](int32_t k, int32_t a, int32_t upto, uint64_t& bv, int32_t& bs) -> bool {
         const int64_t p = a >= 0 ? (int64_t)n0 + a : (int64_t)k;
         const uint64_t* __restrict__ brow = a >= 0 ? W.dcc + (int64_t)a * nch : W.dpc + (int64_t)k * nch;
         uint64_t tv = kNoBits;
@@ -395,30 +401,9 @@ __global__ __launch_bounds__(kWalkThreads) void walk_kernel(WalkArgs W) {
                 bv = fv;
                 bs = __builtin_amdgcn_readlane(ti, f);
             }
-        } else if (__builtin_amdgcn_readlane(ti, kTop - 1) != -1) {
-            // every listed member has been replaced and there may be others: the whole row
-            const uint64_t* __restrict__ row = a >= 0 ? W.dcp + (int64_t)a * cap : W.D + (int64_t)k * cap;
-            v = kNoBits;
-            s = -1;
-            for (int32_t j0 = lane; j0 < n0; j0 += 512) {
-                uint64_t y[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) y[e] = row[j0 + 64 * e < n0 ? j0 + 64 * e : n0 - 1];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int32_t j = j0 + 64 * e;
-                    if (j < n0 && (a >= 0 || j != k) && org[j] < 0 && y[e] <= kInfBits && y[e] < v) {
-                        v = y[e];
-                        s = j;
-                    }
-                }
-            }
-            const uint64_t f = wave_min(v);
-            if (f < bv) {
-                bv = f;
-                bs = __builtin_amdgcn_readlane(s, (int)__builtin_ctzll(__ballot(v == f)));
-            }
+            return false;
         }
+        return __builtin_amdgcn_readlane(ti, kTop - 1) != -1;
     };
     __syncthreads();
     uint64_t next = 0;                                 // this thread's entry of the next candidate's dcc row
@@ -435,8 +420,9 @@ __global__ __launch_bounds__(kWalkThreads) void walk_kernel(WalkArgs W) {
             const int32_t k = !member ? -1 : r < nr ? __builtin_amdgcn_readfirstlane(redo[r]) : slot;
             uint64_t v;
             int32_t s;
-            nearest(k, member ? __builtin_amdgcn_readfirstlane(org[k]) : a, c, v, s);
+            const bool whole = nearest(k, member ? __builtin_amdgcn_readfirstlane(org[k]) : a, c, v, s);
             if (lane == 0) {
+                if (whole) full[atomicAdd(&n_full, 1)] = r;
                 if (member) {
                     res_d[r] = v < kInfBits ? v : kInfBits;
                     res_i[r] = s;
@@ -446,6 +432,58 @@ __global__ __launch_bounds__(kWalkThreads) void walk_kernel(WalkArgs W) {
             }
         }
         lds_barrier();
+        // whole rows, every wave a part of each
+        const int32_t nf = __builtin_amdgcn_readfirstlane(n_full);
+        for (int32_t f0 = 0; f0 < nf; f0 += kWalkFull) {
+            const int32_t nb = nf - f0 < kWalkFull ? nf - f0 : kWalkFull;
+            for (int32_t f = 0; f < nb; ++f) {
+                const int32_t r = __builtin_amdgcn_readfirstlane(full[f0 + f]);
+                const int32_t k = r < nr ? __builtin_amdgcn_readfirstlane(redo[r]) : slot;
+                const int32_t a = r <= nr ? __builtin_amdgcn_readfirstlane(org[k]) : c + (r - nr - 1);
+                const uint64_t* __restrict__ row = a >= 0 ? W.dcp + (int64_t)a * cap : W.D + (int64_t)k * cap;
+                uint64_t y[kWalkOwn], v = kNoBits;
+                int32_t s = -1;
+#pragma unroll
+                for (int u = 0; u < kWalkOwn; ++u) {
+                    const int32_t j = tid + u * kWalkThreads;
+                    y[u] = row[j < n0 ? j : n0 - 1];
+                }
+#pragma unroll
+                for (int u = 0; u < kWalkOwn; ++u) {
+                    const int32_t j = tid + u * kWalkThreads;
+                    if (j < n0 && (a >= 0 || j != k) && own[u] < 0 && y[u] <= kInfBits && y[u] < v) {
+                        v = y[u];
+                        s = j;
+                    }
+                }
+                const uint64_t w = wave_min(v);
+                s = lowest_slot(__ballot(v == w), s);
+                if (lane == 0) {
+                    part_v[f][wv] = w;
+                    part_s[f][wv] = s;
+                }
+            }
+            lds_barrier();
+            if (wv < nb) {
+                const int32_t r = __builtin_amdgcn_readfirstlane(full[f0 + wv]);
+                const uint64_t v = part_v[wv][lane & 15];
+                const int32_t s = part_s[wv][lane & 15];
+                const uint64_t w = uniform(row_min(v));
+                const int32_t best = lowest_slot(__ballot(v == w) & 0xffffull, s);
+                if (lane == 0) {
+                    if (r <= nr) {
+                        if (w < res_d[r]) {
+                            res_d[r] = w;
+                            res_i[r] = best;
+                        }
+                    } else if (w < look_d[r - nr - 1]) {
+                        look_d[r - nr - 1] = w;
+                    }
+                }
+            }
+            lds_barrier();
+        }
+        if (tid == 0 && nf > 0) n_full = 0;
         if (nr >= 0) {
 #pragma unroll
             for (int u = 0; u < kWalkOwn; ++u) {
