@@ -16,11 +16,12 @@
 // The forward and the hidden gradients are the canonical chains (bias or zero
 // first, inputs ascending, one fmaf each) in the order of the layer-by-layer
 // kernels, so their values are the same to the bit; only the sums over the
-// batch (weight gradients, loss) have an order of their own, fixed by B.
+// batch (weight gradients, loss) have an order of their own, fixed by B, the loss
+// in 64 bits.
 //
-// Measured (us per step, before -> now): 3 x 128 fp32 with dropout 135 -> 24 at
-// B = 256, 169 -> 30 at 1,000, 341 -> 83 at 8,192; 64-256-256 bf16 119 -> 30, 174
-// -> 41 and 166 -> 139.  step_rows is about 20 of the 24 us.
+// Measured (us per step, before -> now): 3 x 128 fp32 with dropout 135 -> 22 at
+// B = 256, 169 -> 29 at 1,000, 341 -> 83 at 8,192; 64-256-256 bf16 119 -> 30, 174
+// -> 41 and 166 -> 139.  step_rows is 18 of the 22 us.
 #include <algorithm>
 
 #include "k_policy.h"
@@ -31,7 +32,6 @@ namespace {
 
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kStepThreads = 256;
 constexpr int kStepWidth = 256;               // widest layer (inputs and units)
 constexpr int kStepRow = kStepWidth + 4;      // LDS row of one sample's activations
 
@@ -79,9 +79,7 @@ __device__ __forceinline__ float step_drop(const DropArgs& D, int layer, int64_t
 // offsets, and the weights through LDS in 64 KB chunks of 16-byte loads (21
 // cycles per input, but 3,000 per chunk to fetch and store it; 22.0 against
 // 24.1 us a step at B = 256, 118 against 83 at 8,192).
-constexpr int kStepPre = 16;
-
-template <bool QW, int SP>
+template <bool QW, int SP, int kStepPre>
 __device__ __forceinline__ void step_chain(float (&acc)[SP], const float* __restrict__ w, int64_t ld, int K,
                                            const float* xs) {
     float wa[kStepPre], wb[kStepPre];
@@ -131,13 +129,14 @@ __device__ __forceinline__ void step_chain(float (&acc)[SP], const float* __rest
     }
 }
 
-// G groups of 256 / G threads; a thread is unit (tid % (256 / G)) of its group's
-// SP samples, so a workgroup takes G * SP samples.
-template <bool BF, int G, int SP>
-__global__ __launch_bounds__(kStepThreads) void step_rows_kernel(StepArgs P) {
-    constexpr int W = kStepThreads / G, S = G * SP;
+// G groups of T / G threads; a thread is unit (tid % (T / G)) of its group's SP
+// samples, so a workgroup takes G * SP samples.
+template <bool BF, int T, int G, int SP, int PRE>
+__global__ __launch_bounds__(T) void step_rows_kernel(StepArgs P) {
+    constexpr int W = T / G, S = G * SP;
     __shared__ __align__(16) float xs[2][S * kStepRow];
-    __shared__ float gs[S], w3[kStepWidth];
+    __shared__ float gs[S];
+    __shared__ __align__(16) float w3[kStepWidth];
     const int tid = (int)threadIdx.x, unit = tid % W, grp = tid / W;
     const int64_t b0 = (int64_t)blockIdx.x * S;
     // Every XCD's L2 starts a step without the weights, which the last step's tiles left in memory: a workgroup reads
@@ -148,10 +147,10 @@ __global__ __launch_bounds__(kStepThreads) void step_rows_kernel(StepArgs P) {
         const int share = (int)(gridDim.x + 7) / 8, mine = (int)blockIdx.x / 8;
         const int lc = (P.n_compute + 31) / 32, lines = lc + (P.n_master + 31) / 32;
 #pragma unroll 4
-        for (int q = mine * kStepThreads + tid; q < lines; q += share * kStepThreads)
+        for (int q = mine * T + tid; q < lines; q += share * T)
             touched |= __float_as_uint(q < lc ? P.compute[32 * q] : P.master[32 * (q - lc)]);
     }
-    for (int e = tid; e < S * P.d; e += kStepThreads) {
+    for (int e = tid; e < S * P.d; e += T) {
         const int i = e / P.d, c = e - i * P.d;
         const int64_t b = b0 + i;
         float v = 0.0f;
@@ -164,7 +163,7 @@ __global__ __launch_bounds__(kStepThreads) void step_rows_kernel(StepArgs P) {
         }
         xs[0][i * kStepRow + c] = v;
     }
-    for (int k = tid; k < P.hl; k += kStepThreads) w3[k] = P.compute[P.layer[P.L].wt + k];
+    for (int k = tid; k < P.hl; k += T) w3[k] = P.compute[P.layer[P.L].wt + k];
     asm volatile("" ::"v"(touched));
     __syncthreads();
     // forward; bit i of mask[l]: this thread's unit of sample i is on (z > 0)
@@ -179,7 +178,7 @@ __global__ __launch_bounds__(kStepThreads) void step_rows_kernel(StepArgs P) {
         const float bias = P.compute[P.layer[l].bl + o];
 #pragma unroll
         for (int i = 0; i < SP; ++i) acc[i] = bias;
-        step_chain<false, SP>(acc, P.compute + P.layer[l].wt + o, O, K, xs[cur] + grp * SP * kStepRow);
+        step_chain<false, SP, PRE>(acc, P.compute + P.layer[l].wt + o, O, K, xs[cur] + grp * SP * kStepRow);
         if (unit < O) {
 #pragma unroll
             for (int i = 0; i < SP; ++i) {
@@ -201,11 +200,19 @@ __global__ __launch_bounds__(kStepThreads) void step_rows_kernel(StepArgs P) {
         const float* x = xs[cur] + tid * kStepRow;
         int k = 0;
         for (; k + 16 <= P.hl; k += 16) {
-            float xv[16], wv[16];
+            float4 xv[4], wv[4];
 #pragma unroll
-            for (int e = 0; e < 16; ++e) { xv[e] = x[k + e]; wv[e] = w3[k + e]; }
+            for (int e = 0; e < 4; ++e) {
+                xv[e] = *reinterpret_cast<const float4*>(x + k + 4 * e);
+                wv[e] = *reinterpret_cast<const float4*>(w3 + k + 4 * e);
+            }
 #pragma unroll
-            for (int e = 0; e < 16; ++e) t = __builtin_fmaf(wv[e], xv[e], t);
+            for (int e = 0; e < 4; ++e) {
+                t = __builtin_fmaf(wv[e].x, xv[e].x, t);
+                t = __builtin_fmaf(wv[e].y, xv[e].y, t);
+                t = __builtin_fmaf(wv[e].z, xv[e].z, t);
+                t = __builtin_fmaf(wv[e].w, xv[e].w, t);
+            }
         }
         for (; k < P.hl; ++k) t = __builtin_fmaf(w3[k], x[k], t);
         float gv = 0.0f;
@@ -235,8 +242,8 @@ __global__ __launch_bounds__(kStepThreads) void step_rows_kernel(StepArgs P) {
         } else {
 #pragma unroll
             for (int i = 0; i < SP; ++i) v[i] = 0.0f;
-            step_chain<BF, SP>(v, P.master + P.layer[l + 1].mw + (unit < O ? unit : O - 1), O, P.layer[l + 1].out,
-                               xs[cur] + grp * SP * kStepRow);
+            step_chain<BF, SP, PRE>(v, P.master + P.layer[l + 1].mw + (unit < O ? unit : O - 1), O, P.layer[l + 1].out,
+                                    xs[cur] + grp * SP * kStepRow);
         }
         if (unit < O) {
 #pragma unroll
@@ -267,7 +274,7 @@ constexpr int kStepWaves = 8;
 
 template <bool BF>
 __global__ __launch_bounds__(64 * kStepWaves) void step_weights_kernel(StepArgs P) {
-    __shared__ float red[kStepWaves][256];
+    __shared__ __align__(16) float red[kStepWaves][256];
     __shared__ float redb[kStepWaves][16];
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -282,19 +289,19 @@ __global__ __launch_bounds__(64 * kStepWaves) void step_weights_kernel(StepArgs 
         t -= n;
     }
     if (l > P.L) {                                        // the loss
-        float* lr_ = &red[0][0];
-        float s = 0.0f;
-        for (int b = tid; b < P.B; b += 64 * kStepWaves) s += P.e2[b];
-        lr_[tid] = s;
+        double* sum = reinterpret_cast<double*>(&red[0][0]);
+        double v = 0.0;
+        for (int b = tid; b < P.B; b += 64 * kStepWaves) v += (double)P.e2[b];
+        sum[tid] = v;
         __syncthreads();
         for (int w = 32 * kStepWaves; w > 0; w >>= 1) {
-            if (tid < w) lr_[tid] += lr_[tid + w];
+            if (tid < w) sum[tid] += sum[tid + w];
             __syncthreads();
         }
         if (tid == 0) {
-            const float loss = lr_[0] / (float)P.B;
-            if (P.loss_out) *P.loss_out = loss;
-            if (P.acc) *P.acc = (P.acc_reset ? 0.0 : *P.acc) + (double)loss;
+            const double loss = sum[0] / (double)P.B;
+            if (P.loss_out) *P.loss_out = (float)loss;
+            if (P.acc) *P.acc = (P.acc_reset ? 0.0 : *P.acc) + loss;
         }
         return;
     }
@@ -370,13 +377,23 @@ int step_width(const ModelDims& m) {
     return w;
 }
 
-template <bool BF, int G>
+template <bool BF, int T, int G>
 void launch_rows(const StepArgs& P, int sp, hipStream_t s) {
-    const dim3 block(kStepThreads);
-    auto grid = [&](int S) { return dim3((uint32_t)((P.B + S - 1) / S)); };
-    if (sp == 1) hipLaunchKernelGGL((step_rows_kernel<BF, G, 1>), grid(G), block, 0, s, P);
-    else if (sp == 2) hipLaunchKernelGGL((step_rows_kernel<BF, G, 2>), grid(2 * G), block, 0, s, P);
-    else hipLaunchKernelGGL((step_rows_kernel<BF, G, 4>), grid(4 * G), block, 0, s, P);
+    const dim3 grid((uint32_t)((P.B + G * sp - 1) / (G * sp))), block(T);
+    if (sp == 1) hipLaunchKernelGGL((step_rows_kernel<BF, T, G, 1, 32>), grid, block, 0, s, P);
+    else if (sp == 2) hipLaunchKernelGGL((step_rows_kernel<BF, T, G, 2, 16>), grid, block, 0, s, P);
+    else hipLaunchKernelGGL((step_rows_kernel<BF, T, G, 4, 16>), grid, block, 0, s, P);
+}
+
+template <bool BF>
+void launch_rows_of(const StepArgs& P, int width, int sp, hipStream_t s) {
+    // up to 256 samples of 65 to 128 units go one to a workgroup of two waves: half the loads of a CU per input (22.2
+    // us a step at B = 256 of 3 x 128, 23.6 with two samples on four waves; at 512 it is 28.2 against 25.7)
+    if (width <= 64) launch_rows<BF, 256, 4>(P, sp, s);
+    else if (width <= 128 && P.B <= 256)
+        hipLaunchKernelGGL((step_rows_kernel<BF, 128, 1, 1, 32>), dim3((uint32_t)P.B), dim3(128), 0, s, P);
+    else if (width <= 128) launch_rows<BF, 256, 2>(P, sp, s);
+    else launch_rows<BF, 256, 1>(P, sp, s);
 }
 
 }  // namespace
@@ -424,15 +441,8 @@ hipError_t launch_step_fused(const ModelDims& m, float* master, float* compute, 
     // model, 26 with two), two up to three a CU (30.5 at B = 1,000; 33 with one, 34 with four), then four (83 at
     // B = 8,192; 115 with two, 158 with one): each weight read then serves more samples
     const int sp = B <= 256 * G ? 1 : B <= 768 * G ? 2 : 4;
-    if (m.bf16) {
-        if (G == 4) launch_rows<true, 4>(P, sp, s);
-        else if (G == 2) launch_rows<true, 2>(P, sp, s);
-        else launch_rows<true, 1>(P, sp, s);
-    } else {
-        if (G == 4) launch_rows<false, 4>(P, sp, s);
-        else if (G == 2) launch_rows<false, 2>(P, sp, s);
-        else launch_rows<false, 1>(P, sp, s);
-    }
+    if (m.bf16) launch_rows_of<true>(P, width, sp, s);
+    else launch_rows_of<false>(P, width, sp, s);
     int tiles = 0;
     for (int l = 0; l <= m.L; ++l) tiles += ((m.out_of(l) + 15) / 16) * ((m.in_of(l) + 15) / 16);
     const bool want_loss = loss.step || loss.acc;
