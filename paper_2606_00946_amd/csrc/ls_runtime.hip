@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "ls_internal.h"
+#include "ls_scratch.h"
 #include "k_policy.h"
 
 struct ls_ctx {
@@ -171,7 +172,8 @@ struct DeviceScope {
     }
 };
 
-int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
+using ls::round_up;
+using ls::WsCarve;
 
 // The model that updates act on: the shadow while double buffering, else the live one.
 struct ModelSlot {
@@ -344,19 +346,6 @@ struct Timed {
         t_.done();                           \
         LS_HIP((ctx), e2_);                  \
     } while (0)
-
-struct WsCarve {
-    char* base;
-    size_t cap = SIZE_MAX;   // bytes behind base
-    size_t off = 0;
-    template <class T>
-    T* take(int64_t count) {
-        T* p = reinterpret_cast<T*>(base + off);
-        off += (size_t)round_up(count * (int64_t)sizeof(T), 256);
-        return p;
-    }
-    bool ok() const { return off <= cap; }
-};
 
 }  // namespace
 
@@ -1209,47 +1198,40 @@ int ls_buffer_push(ls_ctx* c, int32_t B, const float* feats, const float* ttft, 
     // workspace
     const int64_t f_fwd = n_all > 0 ? ls::forward_rows_floats(m, n_all) : 0;
     const int64_t adm_bytes = n_all > 0 && nc > 0 ? ls::admission_workspace_bytes(bf.rep_cap, nc) : 0;
-    size_t need = (size_t)round_up((int64_t)(nc + B) * 4, 256)                       // codes
-                  + (size_t)round_up((int64_t)(nc > 0 ? nc : 1) * (d + 1) * 4, 256) + 256     // candidate rows
-                  + (size_t)round_up((int64_t)(n_all > 0 ? n_all : 1) * (d + 1) * 4, 256) + 256  // forward input
-                  + (size_t)round_up(f_fwd * 4, 256)
-                  + (size_t)round_up((int64_t)(nc > 0 ? nc : 1) * H * 8, 256)          // candidate embeddings
-                  + 512 + (size_t)round_up(adm_bytes, 256);                            // the admission's scratch
-    int rc = grow(c, &bf.ws, &bf.ws_cap, need, s);
+    auto carve = [&](WsCarve& w) { return ls::carve_push(w, B, nc, n_all, d, H, f_fwd, adm_bytes); };
+    WsCarve size;
+    (void)carve(size);
+    int rc = grow(c, &bf.ws, &bf.ws_cap, size.off, s);
     if (rc) return rc;
-    WsCarve w{(char*)bf.ws};
-    int32_t* codes = w.take<int32_t>(nc + B);
-    float* cx = w.take<float>((int64_t)(nc > 0 ? nc : 1) * d);
-    float* cy = w.take<float>(nc > 0 ? nc : 1);
-    float* ax = w.take<float>((int64_t)(n_all > 0 ? n_all : 1) * d);
-    float* ay = w.take<float>(n_all > 0 ? n_all : 1);
-    float* fws = w.take<float>(f_fwd > 0 ? f_fwd : 1);
-    double* cemb = w.take<double>((int64_t)(nc > 0 ? nc : 1) * H);
-    int32_t* adm = w.take<int32_t>(64);
-    char* adm_ws = w.take<char>(adm_bytes);
+    WsCarve w{(char*)bf.ws, bf.ws_cap};
+    const ls::PushScratch S = carve(w);
+    if (!w.ok()) return fail(c, LS_ERR_NOMEM, "push scratch smaller than the call's carving (internal sizing error)");
     // stage the codes
     rc = stage_reserve(c, sizeof(int32_t) * (size_t)(nc + B) + 64);
     if (rc) return rc;
     if (nc) memcpy(c->stage, cand.data(), sizeof(int32_t) * (size_t)nc);
     memcpy((int32_t*)c->stage + nc, dst.data(), sizeof(int32_t) * (size_t)B);
-    LS_HIP(c, hipMemcpyAsync(codes, c->stage, sizeof(int32_t) * (size_t)(nc + B), hipMemcpyHostToDevice, s));
+    LS_HIP(c, hipMemcpyAsync(S.codes, c->stage, sizeof(int32_t) * (size_t)(nc + B), hipMemcpyHostToDevice, s));
     LS_HIP(c, hipEventRecord(c->stage_done, s));
     c->stage_pending = true;
     // candidates leave the FIFO before the new rows overwrite it
-    LS_TIMED(c, K_BUFFER, s, ls::launch_gather_rows(codes, nc, d, bf.fifo_x, bf.fifo_y, feats, ttft, cx, cy, s));
-    LS_TIMED(c, K_BUFFER, s, ls::launch_scatter_rows(codes + nc, B, d, feats, ttft, bf.fifo_x, bf.fifo_y, s));
+    LS_TIMED(c, K_BUFFER, s,
+             ls::launch_gather_rows(S.codes, nc, d, bf.fifo_x, bf.fifo_y, feats, ttft, S.cx, S.cy, s));
+    LS_TIMED(c, K_BUFFER, s, ls::launch_scatter_rows(S.codes + nc, B, d, feats, ttft, bf.fifo_x, bf.fifo_y, s));
     if (n_all > 0 && nc > 0) {
         // forward of the pool (slots 0..n0) followed by the candidates
-        LS_HIP(c, hipMemcpyAsync(ax, bf.rep_x, sizeof(float) * (size_t)n0 * d, hipMemcpyDeviceToDevice, s));
-        LS_HIP(c, hipMemcpyAsync(ay, bf.rep_y, sizeof(float) * (size_t)n0, hipMemcpyDeviceToDevice, s));
-        LS_HIP(c, hipMemcpyAsync(ax + (int64_t)n0 * d, cx, sizeof(float) * (size_t)nc * d, hipMemcpyDeviceToDevice, s));
-        LS_HIP(c, hipMemcpyAsync(ay + n0, cy, sizeof(float) * (size_t)nc, hipMemcpyDeviceToDevice, s));
+        LS_HIP(c, hipMemcpyAsync(S.ax, bf.rep_x, sizeof(float) * (size_t)n0 * d, hipMemcpyDeviceToDevice, s));
+        LS_HIP(c, hipMemcpyAsync(S.ay, bf.rep_y, sizeof(float) * (size_t)n0, hipMemcpyDeviceToDevice, s));
+        LS_HIP(c, hipMemcpyAsync(S.ax + (int64_t)n0 * d, S.cx, sizeof(float) * (size_t)nc * d,
+                                 hipMemcpyDeviceToDevice, s));
+        LS_HIP(c, hipMemcpyAsync(S.ay + n0, S.cy, sizeof(float) * (size_t)nc, hipMemcpyDeviceToDevice, s));
         float *a2 = nullptr, *t = nullptr;
         LS_TIMED(c, K_BUFFER, s,
-                 ls::launch_forward_rows(m, train_model(c).compute, c->mu, c->isig, n_all, ax, fws, &a2, &t, s));
+                 ls::launch_forward_rows(m, train_model(c).compute, c->mu, c->isig, n_all, S.ax, S.forward, &a2, &t,
+                                         s));
         LS_TIMED(c, K_BUFFER, s,
-                 ls::launch_admission(a2, t, ay, n0, nc, H, d, bf.rep_cap, cx, cy, cemb, bf.emb, bf.rep_x, bf.rep_y,
-                                      bf.D, admitted ? admitted : adm, adm_ws, s));
+                 ls::launch_admission(a2, t, S.ay, n0, nc, H, d, bf.rep_cap, S.cx, S.cy, S.cemb, bf.emb, bf.rep_x,
+                                      bf.rep_y, bf.D, admitted ? admitted : S.admitted, S.admission, s));
     } else if (admitted) {
         LS_TIMED(c, K_BUFFER, s, ls::launch_fill_u32(reinterpret_cast<uint32_t*>(admitted), 0u, 1, s));
     }
@@ -1322,21 +1304,19 @@ int ls_train_round(ls_ctx* c, int32_t epochs, int32_t batch, float lr, const int
     hipStream_t s = (hipStream_t)stream;
     const ls::ModelDims& m = c->dims;
     const int d = m.d;
-    size_t need = (size_t)round_up((int64_t)epochs * n * 4, 256) + (size_t)round_up((int64_t)batch * (d + 1) * 4, 256) +
-                  512 + (size_t)round_up(ls::update_workspace_bytes(m, batch), 256);
-    int rc = grow(c, &bf.ws, &bf.ws_cap, need, s);
+    const int64_t upd_bytes = ls::update_workspace_bytes(m, batch);
+    auto carve = [&](WsCarve& w) { return ls::carve_train(w, epochs, n, batch, d, upd_bytes); };
+    WsCarve size;
+    (void)carve(size);
+    int rc = grow(c, &bf.ws, &bf.ws_cap, size.off, s);
     if (rc) return rc;
-    WsCarve w{(char*)bf.ws};
-    int32_t* dcodes = w.take<int32_t>((int64_t)epochs * n);
-    float* bx = w.take<float>((int64_t)batch * d);
-    float* by = w.take<float>(batch);
-    float* step_loss = w.take<float>(64);
-    double* acc = w.take<double>(32);
-    void* uws = w.take<char>(ls::update_workspace_bytes(m, batch));
+    WsCarve w{(char*)bf.ws, bf.ws_cap};
+    const ls::TrainScratch S = carve(w);
+    if (!w.ok()) return fail(c, LS_ERR_NOMEM, "round scratch smaller than the call's carving (internal sizing error)");
     rc = stage_reserve(c, sizeof(int32_t) * codes.size() + 64);
     if (rc) return rc;
     memcpy(c->stage, codes.data(), sizeof(int32_t) * codes.size());
-    LS_HIP(c, hipMemcpyAsync(dcodes, c->stage, sizeof(int32_t) * codes.size(), hipMemcpyHostToDevice, s));
+    LS_HIP(c, hipMemcpyAsync(S.codes, c->stage, sizeof(int32_t) * codes.size(), hipMemcpyHostToDevice, s));
     LS_HIP(c, hipEventRecord(c->stage_done, s));
     c->stage_pending = true;
     const ModelSlot TM = train_model(c);
@@ -1345,7 +1325,7 @@ int ls_train_round(ls_ctx* c, int32_t epochs, int32_t batch, float lr, const int
         nb = 0;
         for (int32_t st = 0; st < n; st += batch) {
             const int32_t mb = n - st < batch ? n - st : batch;
-            const int32_t* rows = dcodes + (int64_t)e * n + st;
+            const int32_t* rows = S.codes + (int64_t)e * n + st;
             const bool last = e + 1 == epochs && loss_out;
             const ls::DropArgs D = next_drop(c);
             ++nb;
@@ -1353,19 +1333,19 @@ int ls_train_round(ls_ctx* c, int32_t epochs, int32_t batch, float lr, const int
                 LS_TIMED(c, K_UPDATE, s,
                          ls::launch_step_fused(m, TM.master, TM.compute, c->mu, c->isig, mb,
                                                {rows, bf.fifo_x, bf.fifo_y, bf.rep_x, bf.rep_y}, lr,
-                                               {nullptr, last ? acc : nullptr, nb == 1}, nullptr, uws, D,
-                                               s));
+                                               {nullptr, last ? S.loss_sum : nullptr, nb == 1}, nullptr, S.update,
+                                               D, s));
                 continue;
             }
             LS_TIMED(c, K_UPDATE, s,
-                     ls::launch_gather_rows(rows, mb, d, bf.fifo_x, bf.fifo_y, bf.rep_x, bf.rep_y, bx, by, s));
+                     ls::launch_gather_rows(rows, mb, d, bf.fifo_x, bf.fifo_y, bf.rep_x, bf.rep_y, S.bx, S.by, s));
             LS_TIMED(c, K_UPDATE, s,
-                     ls::launch_update(m, TM.master, TM.compute, c->mu, c->isig, mb, bx, by, lr, step_loss, nullptr,
-                                       uws, D, c->n_cu, s));
-            if (last) LS_HIP(c, ls::launch_loss_accumulate(step_loss, acc, nb == 1, s));
+                     ls::launch_update(m, TM.master, TM.compute, c->mu, c->isig, mb, S.bx, S.by, lr, S.step_loss,
+                                       nullptr, S.update, D, c->n_cu, s));
+            if (last) LS_HIP(c, ls::launch_loss_accumulate(S.step_loss, S.loss_sum, nb == 1, s));
         }
     }
-    if (loss_out) LS_HIP(c, ls::launch_loss_finish(acc, nb, loss_out, s));
+    if (loss_out) LS_HIP(c, ls::launch_loss_finish(S.loss_sum, nb, loss_out, s));
     if (TM.frag16)
         LS_TIMED(c, K_UPDATE, s,
                  ls::launch_prepare_mfma(ls::make_mfma_layout(c->dims), TM.master, TM.frag16, TM.frag32, s));

@@ -1,6 +1,8 @@
 """Online-learning data path through the C ABI against the oracle: the FIFO and
 the gradient-coreset replay pool hold exactly the oracle's rows after every
 push, and a retraining round gives the oracle's weights."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -126,4 +128,27 @@ def test_buffer_errors():
         ctx.ls_train_round(1, 4, 0.01, perm=np.array([0, 0, 1, 2], np.int32))
     assert e.value.code == lodestar.LS_ERR_INVALID
     torch.cuda.synchronize()
+    ctx.close()
+
+
+def test_train_round_scratch_of_whole_mib():
+    """A round whose scratch comes to exactly 2 MiB, the unit it is allocated in:
+    nothing behind the last array is there by rounding.  Weights as the oracle's."""
+    w = synth.generate(dataclasses.replace(synth.CONFIGS["tiny"], d=32, hidden=(32, 32, 32), update_batch=2007))
+    cfg = w.cfg
+    n, epochs = 2007, 2
+    ctx = _ctx(w)
+    ctx.ls_buffer_init(n, 0)
+    note(f"train round with {n} rows a minibatch")
+    ctx.ls_buffer_push(to_dev(w.upd_feats), to_dev(w.upd_ttft))
+    ob = oracle.Buffer(cfg.d, n, 0)
+    oracle.buffer_push("fp32", cfg.hidden, w.params, w.mu, w.inv_sigma, ob, w.upd_feats, w.upd_ttft)
+    perm = np.concatenate([np.random.default_rng(e).permutation(n) for e in range(epochs)]).astype(np.int32)
+    ctx.ls_train_round(epochs, n, w.lr, perm, None)
+    got = ctx.ls_get_model()[0]
+    want, _ = oracle.train_round("fp32", cfg.hidden, w.params, w.mu, w.inv_sigma, ob, epochs, n, w.lr, perm)
+    for lname, a, b in layer_slices(cfg.d, cfg.hidden):
+        dg = got[a:b].astype(np.float64) - w.params[a:b]
+        dw = want[a:b].astype(np.float64) - w.params[a:b]
+        assert np.linalg.norm(dg - dw) <= 1e-4 * np.linalg.norm(dw) + 1e-12, lname
     ctx.close()
