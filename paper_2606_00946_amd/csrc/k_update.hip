@@ -138,6 +138,14 @@ int64_t update_workspace_bytes(const ModelDims& m, int32_t B) {
     return step_fused(m, B) ? step_workspace_bytes(m, B) : plan_ws(m, B, nullptr).bytes;
 }
 
+// The gradient partials are not monotone in B (16,384 samples make 256 chunks of
+// 64, 16,385 make 205 of 80): the last minibatch may need more than a full one.
+int64_t round_workspace_bytes(const ModelDims& m, int32_t n, int32_t batch) {
+    const int32_t full = std::min(batch, n), rest = n % batch;
+    const int64_t bytes = update_workspace_bytes(m, full);
+    return rest > 0 ? std::max(bytes, update_workspace_bytes(m, rest)) : bytes;
+}
+
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------

@@ -352,8 +352,10 @@ hipError_t launch_step_fused(const ModelDims& m, float* master, float* compute, 
                              int32_t B, const StepRows& rows, float lr, const StepLoss& loss, float* grad_out,
                              void* workspace, const DropArgs& drop, hipStream_t s);
 
-// Online update.  Workspace layout is chosen by update_workspace_floats().
+// Online update: workspace of one step, and of a round over n samples in
+// minibatches of `batch` (the last may be smaller).
 int64_t update_workspace_bytes(const ModelDims& m, int32_t B);
+int64_t round_workspace_bytes(const ModelDims& m, int32_t n, int32_t batch);
 hipError_t launch_update(const ModelDims& m, float* master, float* compute, const float* mu,
                          const float* inv_sigma, int32_t B, const float* feats, const float* ttft, float lr,
                          float* loss_out, float* grad_out, void* workspace, const DropArgs& drop, int n_cu,

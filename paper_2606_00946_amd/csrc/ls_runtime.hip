@@ -1304,8 +1304,8 @@ int ls_train_round(ls_ctx* c, int32_t epochs, int32_t batch, float lr, const int
     hipStream_t s = (hipStream_t)stream;
     const ls::ModelDims& m = c->dims;
     const int d = m.d;
-    const int64_t upd_bytes = ls::update_workspace_bytes(m, batch);
-    auto carve = [&](WsCarve& w) { return ls::carve_train(w, epochs, n, batch, d, upd_bytes); };
+    const int64_t upd_bytes = ls::round_workspace_bytes(m, n, batch);
+    auto carve = [&](WsCarve& w) { return ls::carve_train(w, epochs, n, std::min(batch, n), d, upd_bytes); };
     WsCarve size;
     (void)carve(size);
     int rc = grow(c, &bf.ws, &bf.ws_cap, size.off, s);

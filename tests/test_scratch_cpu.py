@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+from paper_2606_00946_amd import build
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PKG = os.path.join(ROOT, "paper_2606_00946_amd")
 
@@ -78,3 +80,48 @@ def test_train_scratch(program, epochs, n, batch, d, update):
 def test_push_scratch(program, B, nc, n_all, d, H, forward, admission):
     _fits(program("push", B, nc, n_all, d, H, forward, admission),
           [4 * (nc + B), 4 * nc * d, 4 * nc, 4 * n_all * d, 4 * n_all, 4 * forward, 8 * nc * H, 4, admission])
+
+
+ROUND_PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "ls_internal.h"
+
+// argv: d, hidden layers, width, bf16, rows, minibatch.  The round's workspace and each of its steps'.
+int main(int, char** a) {
+    ls_model_config cfg{};
+    cfg.d = atoi(a[1]);
+    cfg.n_hidden = atoi(a[2]);
+    for (int l = 0; l < cfg.n_hidden; ++l) cfg.hidden[l] = atoi(a[3]);
+    cfg.dtype = atoi(a[4]) ? LS_BF16 : LS_FP32;
+    cfg.block_tokens = 16;
+    const ls::ModelDims m = ls::make_dims(cfg);
+    const int n = atoi(a[5]), batch = atoi(a[6]);
+    printf("%lld", (long long)ls::round_workspace_bytes(m, n, batch));
+    for (int b : {batch < n ? batch : n, n % batch})
+        if (b > 0) printf(" %lld", (long long)ls::update_workspace_bytes(m, b));
+    printf("\n");
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def round_program(tmp_path_factory):
+    d = tmp_path_factory.mktemp("round")
+    src, exe = str(d / "round.cpp"), str(d / "round")
+    with open(src, "w") as f:
+        f.write(ROUND_PROGRAM)
+    subprocess.check_call([build.HIPCC, "-std=c++17", "-O1", "-I", build.CSRC, "-I", build.INCLUDE, src, "-o", exe,
+                           "-L", PKG, "-l:liblodestar.so", f"-Wl,-rpath,{PKG}"])
+    return lambda *args: [int(v) for v in subprocess.check_output([exe, *map(str, args)], text=True).split()]
+
+
+# a last minibatch one row short of a full one, where a full one's gradients take
+# fewer and larger chunks; two-launch steps; a minibatch larger than the round
+@pytest.mark.parametrize("d,layers,width,bf16,n,batch",
+                         [(64, 2, 256, 0, 32769, 16385), (16, 2, 64, 0, 65537, 32769), (32, 3, 128, 1, 32769, 16385),
+                          (64, 2, 512, 0, 16385, 8193), (64, 2, 256, 1, 16385, 8193), (16, 2, 64, 0, 1000, 300),
+                          (16, 1, 64, 0, 20, 4096), (37, 2, 300, 0, 16384, 16385)])
+def test_round_workspace_holds_every_minibatch(round_program, d, layers, width, bf16, n, batch):
+    whole, *steps = round_program(d, layers, width, bf16, n, batch)
+    assert steps and whole >= max(steps)
