@@ -67,7 +67,7 @@ __device__ __forceinline__ float act(float z) {
 
 // LIST: score the pairs list[0 .. *count) (pair indices r * N + i), with
 // persistent workgroups that take 32 NG list entries at a time; otherwise every
-// pair, 32 NG per workgroup.
+// pair, 32 NG per workgroup (more than chain_groups() launches: in turns).
 template <bool BF, int H, int NG, bool LIST>
 __device__ __forceinline__ void chain_body(const ChainModel& M, const float* __restrict__ mu,
                                            const float* __restrict__ isig, const float* __restrict__ part_t,
@@ -84,7 +84,8 @@ __device__ __forceinline__ void chain_body(const ChainModel& M, const float* __r
     const int u0 = 64 * __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // the wave's first unit
     const int64_t cnt = LIST ? (int64_t)*count : (int64_t)R * N;
     float* __restrict__ row = hl + col * LDH;                          // group n's: row + n * 32 LDH
-    for (int64_t e0 = (int64_t)blockIdx.x * NP; e0 < cnt; e0 += (int64_t)gridDim.x * NP) {
+    const int64_t turn = (int64_t)gridDim.x * NP;
+    for (int64_t e0 = (int64_t)blockIdx.x * NP; e0 < cnt; e0 += turn) {
         float xt[NG][5];
         int32_t inst[NG];
 #pragma unroll
@@ -194,7 +195,7 @@ __device__ __forceinline__ void chain_body(const ChainModel& M, const float* __r
             const int64_t e = e0 + (int)threadIdx.x;
             scores[LIST ? list[e] : e] = t;
         }
-        if (LIST) __syncthreads();                                     // the tile is the next group's
+        if (e0 + turn < cnt) __syncthreads();                          // the tile is the next group's
     }
 }
 
@@ -361,6 +362,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void re
                                  scores);
 }
 
+uint32_t chain_groups(int64_t pairs, int per_group, int threads) {
+    const int64_t want = (pairs + per_group - 1) / per_group, most = (int64_t)UINT32_MAX / threads;
+    return (uint32_t)(want < most ? want : most);
+}
+
 namespace {
 
 template <bool BF, int H, int NG>
@@ -375,9 +381,8 @@ hipError_t launch_chain(const ChainModel& M, const float* mu, const float* isig,
         hipLaunchKernelGGL((rescore_chain_mfma_kernel<BF, H, NG>), dim3((uint32_t)(n_cu * per_cu)), dim3(H), lds, s, M, mu,
                            isig, part_t, R, N, req_off, prompt_len, overlap, block_tokens, list, count, scores);
     } else {
-        const int64_t grid = ((int64_t)R * N + NG * kChainPairs - 1) / (NG * kChainPairs);
-        hipLaunchKernelGGL((score_chain_mfma_kernel<BF, H, NG>), dim3((uint32_t)grid), dim3(H), lds, s, M, mu,
-                           isig, part_t, R, N, req_off, prompt_len, overlap, block_tokens, scores);
+        hipLaunchKernelGGL((score_chain_mfma_kernel<BF, H, NG>),
+                           dim3(chain_groups((int64_t)R * N, NG * kChainPairs, H)), dim3(H), lds, s, M, mu, isig, part_t, R, N, req_off, prompt_len, overlap, block_tokens, scores);
     }
     return hipGetLastError();
 }
@@ -395,9 +400,8 @@ hipError_t launch_wave(const PairModel& M, const float* mu, const float* isig, c
                            s, M, mu, isig, part_t, R, N, req_off, prompt_len, overlap, block_tokens, list, count,
                            scores);
     } else {
-        const int64_t grid = ((int64_t)R * N + kChainPairs - 1) / kChainPairs;
-        hipLaunchKernelGGL((score_wave_mfma_kernel<BF, H1, H2>), dim3((uint32_t)grid), dim3(64), lds, s, M, mu,
-                           isig, part_t, R, N, req_off, prompt_len, overlap, block_tokens, scores);
+        hipLaunchKernelGGL((score_wave_mfma_kernel<BF, H1, H2>),
+                           dim3(chain_groups((int64_t)R * N, kChainPairs, 64)), dim3(64), lds, s, M, mu, isig, part_t, R, N, req_off, prompt_len, overlap, block_tokens, scores);
     }
     return hipGetLastError();
 }

@@ -247,6 +247,10 @@ hipError_t launch_score_pairs(const ModelDims& m, const float* compute, const fl
 // count (device; both or neither) only the pairs list[0 .. *count) are scored,
 // as launch_rescore does.
 bool chain_mfma_supported(const ModelDims& m);
+// Workgroups for `pairs` at `per_group` pairs and `threads` threads each: no
+// more than one launch takes (fewer than 2^32 threads); the kernels take the
+// rest in turns.
+uint32_t chain_groups(int64_t pairs, int per_group, int threads);
 hipError_t launch_score_chain_mfma(const ModelDims& m, const float* compute, const float* mu, const float* inv_sigma,
                                    const float* part_t, int32_t R, int32_t N, const int64_t* req_off,
                                    const int32_t* prompt_len, const int32_t* overlap, const int64_t* list,
