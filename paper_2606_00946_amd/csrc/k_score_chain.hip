@@ -439,6 +439,10 @@ bool chain_mfma_supported(const ModelDims& m) {
     return m.d == m.d_inst + 5 && (m.h[0] == 64 || m.h[0] == 128 || m.h[0] == 256);
 }
 
+bool chain_scores(const ModelDims& m) { return m.mfma_chains && chain_mfma_supported(m); }
+
+bool scores_by_layer(const ModelDims& m) { return m.L != 2 && !chain_scores(m); }
+
 hipError_t launch_score_chain_mfma(const ModelDims& m, const float* compute, const float* mu, const float* inv_sigma,
                                    const float* part_t, int32_t R, int32_t N, const int64_t* req_off,
                                    const int32_t* prompt_len, const int32_t* overlap, const int64_t* list,

@@ -242,11 +242,18 @@ hipError_t launch_instance_partial(const ModelDims& m, const float* compute, con
 hipError_t launch_score_pairs(const ModelDims& m, const float* compute, const float* mu, const float* inv_sigma,
                               const float* part_t, int32_t R, int32_t N, const int64_t* req_off,
                               const int32_t* prompt_len, const int32_t* overlap, float* scores, hipStream_t s);
-// The same canonical scores on the matrix cores (two hidden layers of equal
-// width 64, 128 or 256): bit-identical to launch_score_pairs.  With list and
+// Canonical scores on the matrix cores (one to three hidden layers of equal
+// width 64, 128 or 256): bit-identical to launch_score_pairs and
+// launch_score_generic.  With list and
 // count (device; both or neither) only the pairs list[0 .. *count) are scored,
 // as launch_rescore does.
 bool chain_mfma_supported(const ModelDims& m);
+// Whether canonical scores come from these kernels, and whether from the
+// layer-by-layer forward (which takes scratch of its own): the sizing of a
+// scoring call and its launches both ask these.  Neither: two hidden layers on
+// the vector ALUs.
+bool chain_scores(const ModelDims& m);
+bool scores_by_layer(const ModelDims& m);
 // Workgroups for `pairs` at `per_group` pairs and `threads` threads each: no
 // more than one launch takes (fewer than 2^32 threads); the kernels take the
 // rest in turns.
@@ -303,8 +310,8 @@ hipError_t launch_rescore(const ModelDims& m, const float* compute, const float*
 int64_t forward_rows_floats(const ModelDims& m, int32_t B);
 hipError_t launch_forward_rows(const ModelDims& m, const float* compute, const float* mu, const float* isig, int32_t B,
                                const float* feats, float* ws, float** alast_out, float** t_out, hipStream_t s);
-// Scores of all R x N pairs for models without two hidden layers, in chunks
-// through the same forward; ws holds generic_score_floats(m, R * N) floats.
+// Scores of all R x N pairs in chunks through the same forward (where
+// scores_by_layer); ws holds generic_score_floats(m, R * N) floats.
 int64_t generic_score_floats(const ModelDims& m, int64_t pairs);
 hipError_t launch_score_generic(const ModelDims& m, const float* compute, const float* mu, const float* isig,
                                 int32_t R, int32_t N, const int64_t* req_off, const int32_t* prompt_len,

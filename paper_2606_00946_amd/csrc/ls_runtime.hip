@@ -759,17 +759,12 @@ int check_batch(ls_ctx* c, int32_t R, int32_t N, const int64_t* req_off, const u
 // candidate band alone).
 bool fast_path(const ls_ctx* c, const float* scores) { return c->frag16 && !c->exact_scores && scores == nullptr; }
 
-// Whether a scoring call takes the layer-by-layer forward (and its scratch):
-// models other than two hidden layers.  The sizing below and run_pipeline both
-// ask this.
-bool layer_by_layer(const ls::ModelDims& m) { return m.L != 2; }
-
 size_t pipeline_bytes(ls_ctx* c, int32_t R, int32_t N, bool have_overlap, bool have_scores, bool fast) {
     const ls::ModelDims& m = c->dims;
     const int64_t pairs = (int64_t)R * N;
     size_t need = (size_t)round_up((int64_t)m.h1 * N * 4, 256);
     need += (size_t)round_up(ls::prefix_workspace_bytes(R, N), 256);
-    if (layer_by_layer(m)) need += (size_t)round_up(4 * ls::generic_score_floats(m, pairs), 256);
+    if (ls::scores_by_layer(m)) need += (size_t)round_up(4 * ls::generic_score_floats(m, pairs), 256);
     if (!have_overlap) need += (size_t)round_up(pairs * 4, 256);
     if (!have_scores) need += (size_t)round_up(pairs * 4, 256);
     if (fast) {
@@ -810,9 +805,8 @@ int run_pipeline(ls_ctx* c, WsCarve& w, int32_t R, int32_t N, const int64_t* req
                                                          c->prefix_join),
                                      c->prefix_closed, s));
     const uint8_t* band = nullptr;
-    const bool chain = m.mfma_chains && ls::chain_mfma_supported(m);
-    if (layer_by_layer(m) && !chain) {
-        // other depths and unequal widths: the pairs' rows through the layer-by-layer canonical forward
+    if (ls::scores_by_layer(m)) {
+        // the pairs' rows through the layer-by-layer canonical forward
         float* gws = w.take<float>(ls::generic_score_floats(m, pairs));
         if (!w.ok()) return fail(c, LS_ERR_NOMEM, "%s", undersized);
         LS_TIMED(c, K_SCORE, s,
@@ -851,7 +845,7 @@ int run_pipeline(ls_ctx* c, WsCarve& w, int32_t R, int32_t N, const int64_t* req
                       ls::launch_rescore(m, c->compute, c->mu, c->isig, part_t, R, N, req_off, prompt_len, ov, list,
                                          count + 32, sc, c->n_cu, s));
         band = flags;
-    } else if (chain) {
+    } else if (ls::chain_scores(m)) {
         LS_TIMED_NEXT(c, K_SCORE, s,
                       ls::launch_score_chain_mfma(m, c->compute, c->mu, c->isig, part_t, R, N, req_off, prompt_len, ov,
                                                   nullptr, nullptr, c->n_cu, sc, s));

@@ -11,7 +11,7 @@ import pytest
 
 import oracle
 from gpu_helpers import GpuRun, note
-from paper_2606_00946_amd import synth
+from paper_2606_00946_amd import lodestar, synth
 from test_gpu_depth import mode_of
 
 pytestmark = pytest.mark.gpu
@@ -52,3 +52,28 @@ def test_rescored_minima_bit_for_bit(d, hidden):
         assert np.array_equal(got["chosen"], want["chosen"]), (R, N)
         assert np.array_equal(got["min_ttft"], want["scores"].astype(np.float32).min(1)), (R, N)
         run.ctx.close()
+
+
+def test_three_layers_fit_the_allocation_free_call():
+    """69,300 pairs of 3 x 128: the chain kernels take no scratch per layer, so
+    the batch fits ls_score_batch_noalloc; layer by layer it does not."""
+    import torch
+    cfg = dataclasses.replace(synth.CONFIGS["homogeneous"], hidden=(128, 128, 128), R=2100, N=33,
+                              capacity=tuple(2000 for _ in synth.CONFIGS["homogeneous"].capacity), warmup_requests=0,
+                              update_batch=64)
+    w = synth.generate(cfg)
+    run = GpuRun(w)
+    note("three layers, allocation-free scoring of 69,300 pairs")
+    want = run.score(with_scores=False)
+    chosen = torch.full((cfg.R,), -7, dtype=torch.int32, device="cuda")
+    mt = torch.zeros(cfg.R, device="cuda")
+    args = (run.req_off, run.req_hashes, run.prompt_len, run.inst_feat, chosen, mt)
+    run.ctx.ls_score_batch_noalloc(*args)
+    torch.cuda.synchronize()
+    assert np.array_equal(chosen.cpu().numpy(), want["chosen"])
+    assert np.array_equal(mt.cpu().numpy(), want["min_ttft"])
+    run.ctx.ls_set_chain_kernels(1)
+    with pytest.raises(lodestar.LodestarError) as e:
+        run.ctx.ls_score_batch_noalloc(*args)
+    assert e.value.code == lodestar.LS_ERR_INVALID
+    run.ctx.close()
