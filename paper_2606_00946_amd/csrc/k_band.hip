@@ -580,7 +580,7 @@ hipError_t launch_rescore(const ModelDims& m, const float* compute, const float*
                           const int32_t* prompt_len, const int32_t* overlap, const int64_t* list,
                           const uint32_t* count, float* scores, int n_cu, hipStream_t s) {
     // the same chains as K=1 fp32 matrix-core steps (bit-identical), 32 candidates per wave
-    if (chain_scores(m))
+    if (chain_scores(m, N))
         return launch_score_chain_mfma(m, compute, mu, inv_sigma, part_t, R, N, req_off, prompt_len, overlap, list,
                                        count, n_cu, scores, s);
     PairModel M{compute + m.c_w1, compute + m.c_w2t, compute + m.c_b2, compute + m.c_w3, compute + m.c_b3,

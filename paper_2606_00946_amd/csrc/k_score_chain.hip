@@ -126,7 +126,7 @@ __device__ __forceinline__ void chain_body(const ChainModel& M, const float* __r
         for (int n = 0; n < NG; ++n)
 #pragma unroll
             for (int i = 0; i < 32; ++i)
-                acc[n][i] = part_t[(uint32_t)((unit4(i >> 2) + (i & 3)) * N + inst[n])];   // h1 N < 2^31
+                acc[n][i] = part_t[(uint32_t)(unit4(i >> 2) + (i & 3)) * (uint32_t)N + (uint32_t)inst[n]];
         {
             const float* __restrict__ w1 = M.w1t + (int64_t)M.d_inst * H + u0 + lane;
             float a[5];
@@ -243,10 +243,10 @@ __device__ __forceinline__ void wave_body(const PairModel& M, const float* __res
     // loop instead of holding b2, w3, W1 columns, W2T rows and partial addresses
     // in registers across tasks
     // (an opaque zero offset: the pointers keep their global address space)
-    int32_t z0 = 0;
+    uint32_t z0 = 0;
     asm volatile("" : "+s"(z0));
     const float *w1b = M.w1 + z0, *w2b = M.w2t + z0, *b2b = M.b2 + z0, *w3b = M.w3 + z0, *ptb = part_t + z0;
-    const int32_t Nb = N + z0;
+    const uint32_t Nb = (uint32_t)N + z0;
     const int64_t e = e0 + col < cnt ? e0 + col : cnt - 1;       // lanes past the end score a valid pair
     const int64_t q = LIST ? list[e] : e;
     const int64_t r = q / N;
@@ -263,7 +263,7 @@ __device__ __forceinline__ void wave_body(const PairModel& M, const float* __res
 #pragma unroll
         for (int i = 0; i < 32; ++i) {
             const int u = 64 * p + 32 * (i >> 4) + 8 * ((i & 15) >> 2) + 4 * hi + (i & 3);
-            acc[i] = ptb[(uint32_t)(u * Nb + inst)];           // h1 N < 2^31
+            acc[i] = ptb[(uint32_t)u * Nb + (uint32_t)inst];
         }
         const float* __restrict__ w1 = w1b + (int64_t)(64 * p + lane) * M.d + M.d_inst;
         float a[5];
@@ -439,16 +439,19 @@ bool chain_mfma_supported(const ModelDims& m) {
     return m.d == m.d_inst + 5 && (m.h[0] == 64 || m.h[0] == 128 || m.h[0] == 256);
 }
 
-bool chain_scores(const ModelDims& m) { return m.mfma_chains && chain_mfma_supported(m); }
+// The kernels index the instance partials [h][N] in 32 bits.
+bool chain_scores(const ModelDims& m, int32_t N) {
+    return m.mfma_chains && chain_mfma_supported(m) && (int64_t)m.h[0] * N <= (int64_t)UINT32_MAX + 1;
+}
 
-bool scores_by_layer(const ModelDims& m) { return m.L != 2 && !chain_scores(m); }
+bool scores_by_layer(const ModelDims& m, int32_t N) { return m.L != 2 && !chain_scores(m, N); }
 
 hipError_t launch_score_chain_mfma(const ModelDims& m, const float* compute, const float* mu, const float* inv_sigma,
                                    const float* part_t, int32_t R, int32_t N, const int64_t* req_off,
                                    const int32_t* prompt_len, const int32_t* overlap, const int64_t* list,
                                    const uint32_t* count, int n_cu, float* scores, hipStream_t s) {
     if ((int64_t)R * N <= 0) return hipSuccess;
-    if (!chain_mfma_supported(m) || (list == nullptr) != (count == nullptr)) return hipErrorInvalidValue;
+    if (!chain_scores(m, N) || (list == nullptr) != (count == nullptr)) return hipErrorInvalidValue;
     ChainModel M{};
     M.w1t = compute + m.c_wt[0];
     M.mids = m.L - 1;

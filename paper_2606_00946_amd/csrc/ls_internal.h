@@ -252,8 +252,8 @@ bool chain_mfma_supported(const ModelDims& m);
 // layer-by-layer forward (which takes scratch of its own): the sizing of a
 // scoring call and its launches both ask these.  Neither: two hidden layers on
 // the vector ALUs.
-bool chain_scores(const ModelDims& m);
-bool scores_by_layer(const ModelDims& m);
+bool chain_scores(const ModelDims& m, int32_t N);
+bool scores_by_layer(const ModelDims& m, int32_t N);
 // Workgroups for `pairs` at `per_group` pairs and `threads` threads each: no
 // more than one launch takes (fewer than 2^32 threads); the kernels take the
 // rest in turns.

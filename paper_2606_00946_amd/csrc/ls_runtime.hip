@@ -764,7 +764,7 @@ size_t pipeline_bytes(ls_ctx* c, int32_t R, int32_t N, bool have_overlap, bool h
     const int64_t pairs = (int64_t)R * N;
     size_t need = (size_t)round_up((int64_t)m.h1 * N * 4, 256);
     need += (size_t)round_up(ls::prefix_workspace_bytes(R, N), 256);
-    if (ls::scores_by_layer(m)) need += (size_t)round_up(4 * ls::generic_score_floats(m, pairs), 256);
+    if (ls::scores_by_layer(m, N)) need += (size_t)round_up(4 * ls::generic_score_floats(m, pairs), 256);
     if (!have_overlap) need += (size_t)round_up(pairs * 4, 256);
     if (!have_scores) need += (size_t)round_up(pairs * 4, 256);
     if (fast) {
@@ -805,7 +805,7 @@ int run_pipeline(ls_ctx* c, WsCarve& w, int32_t R, int32_t N, const int64_t* req
                                                          c->prefix_join),
                                      c->prefix_closed, s));
     const uint8_t* band = nullptr;
-    if (ls::scores_by_layer(m)) {
+    if (ls::scores_by_layer(m, N)) {
         // the pairs' rows through the layer-by-layer canonical forward
         float* gws = w.take<float>(ls::generic_score_floats(m, pairs));
         if (!w.ok()) return fail(c, LS_ERR_NOMEM, "%s", undersized);
@@ -845,7 +845,7 @@ int run_pipeline(ls_ctx* c, WsCarve& w, int32_t R, int32_t N, const int64_t* req
                       ls::launch_rescore(m, c->compute, c->mu, c->isig, part_t, R, N, req_off, prompt_len, ov, list,
                                          count + 32, sc, c->n_cu, s));
         band = flags;
-    } else if (ls::chain_scores(m)) {
+    } else if (ls::chain_scores(m, N)) {
         LS_TIMED_NEXT(c, K_SCORE, s,
                       ls::launch_score_chain_mfma(m, c->compute, c->mu, c->isig, part_t, R, N, req_off, prompt_len, ov,
                                                   nullptr, nullptr, c->n_cu, sc, s));

@@ -16,15 +16,16 @@ PROGRAM = r"""
 // argv: what to ask, then its numbers
 int main(int, char** a) {
     if (!strcmp(a[1], "groups")) printf("%u\n", ls::chain_groups(atoll(a[2]), atoi(a[3]), atoi(a[4])));
-    if (!strcmp(a[1], "route")) {              // chain kernels on?, input columns, then the hidden widths
+    if (!strcmp(a[1], "route")) {              // chain kernels on?, instances, then the hidden widths
         ls_model_config cfg{};
-        cfg.d = atoi(a[3]);
+        cfg.d = 32;
+        const int N = atoi(a[3]);
         for (char** w = a + 4; *w; ++w) cfg.hidden[cfg.n_hidden++] = atoi(*w);
         cfg.dtype = LS_FP32;
         cfg.block_tokens = 16;
         ls::ModelDims m = ls::make_dims(cfg);
         m.mfma_chains = atoi(a[2]) != 0;
-        printf("%d %d\n", ls::chain_scores(m) ? 1 : 0, ls::scores_by_layer(m) ? 1 : 0);
+        printf("%d %d\n", ls::chain_scores(m, N) ? 1 : 0, ls::scores_by_layer(m, N) ? 1 : 0);
     }
 }
 """
@@ -59,5 +60,14 @@ def test_chain_launch_fits(ask, pairs, per_group, threads):
                          [((64,), 1, 0), ((128, 128), 1, 0), ((256, 256, 256), 1, 0), ((96,), 0, 1), ((96, 96), 0, 0),
                           ((128, 64), 0, 0), ((128, 64, 128), 0, 1), ((512, 512, 512), 0, 1)])
 def test_one_route_for_sizing_and_launching(ask, hidden, chain, by_layer):
-    assert ask("route", 1, 32, *hidden) == [chain, by_layer]
-    assert ask("route", 0, 32, *hidden) == [0, int(len(hidden) != 2)]
+    assert ask("route", 1, 64, *hidden) == [chain, by_layer]
+    assert ask("route", 0, 64, *hidden) == [0, int(len(hidden) != 2)]
+
+
+# the chain kernels index the instance partials, h x N, in 32 bits; more goes to
+# the scorers that index in 64
+@pytest.mark.parametrize("hidden", [(64,), (256,), (256, 256), (128, 128, 128)])
+def test_instances_within_the_index(ask, hidden):
+    most = (1 << 32) // hidden[0]
+    assert ask("route", 1, most, *hidden) == [1, 0]
+    assert ask("route", 1, most + 1, *hidden) == [0, int(len(hidden) != 2)]
