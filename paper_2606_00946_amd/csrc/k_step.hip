@@ -17,7 +17,7 @@
 // first, inputs ascending, one fmaf each) in the order of the layer-by-layer
 // kernels, so their values are the same to the bit; only the sums over the
 // batch (weight gradients, loss) have an order of their own, fixed by B, the loss
-// in 64 bits.
+// and the bias gradients in 64 bits.
 //
 // Measured (us per step, before -> now): 3 x 128 fp32 with dropout 135 -> 22 at
 // B = 256, 169 -> 29 at 1,000, 341 -> 83 at 8,192; 64-256-256 bf16 119 -> 30, 174
@@ -263,19 +263,22 @@ __global__ __launch_bounds__(T) void step_rows_kernel(StepArgs P) {
 // ---------------------------------------------------------------------------
 // A workgroup per 16 x 16 tile of one layer's weights; eight waves share the
 // samples, four consecutive ones per v_mfma_f32_16x16x4_f32 step, groups of
-// four dealt to the waves in turn and, within a wave, to four accumulators (a
-// sum has B / 128 terms in sequence: no more than the 64 of the split-K kernel
-// it replaces up to B = 8,192, and four independent matrix-core chains).  Each
-// operand is read straight from the sample-major arrays, 64 bytes per row.  The
-// workgroups of a layer's first input tile also sum its bias gradient.  The last
-// workgroup reduces the loss.
+// four dealt to the waves in turn and, within a wave, to four accumulators: four
+// independent matrix-core chains of B / 128 instructions, B / 32 products each
+// (256 at B = 8,192; the split-K kernel of larger batches sums 64 and then its
+// chunks in sequence, and its errors against 64 bits are larger throughout:
+// 1.7e-7 against 5e-8 there).  Each operand is read straight from the
+// sample-major arrays, 64 bytes per row.  The workgroups of a layer's first
+// input tile also sum its bias gradient, in 64 bits: one fp32 sum of B / 32 terms
+// a lane was off by up to 64 units in the last place where they have one sign.
+// The last workgroup reduces the loss.
 // ---------------------------------------------------------------------------
 constexpr int kStepWaves = 8;
 
 template <bool BF>
 __global__ __launch_bounds__(64 * kStepWaves) void step_weights_kernel(StepArgs P) {
     __shared__ __align__(16) float red[kStepWaves][256];
-    __shared__ float redb[kStepWaves][16];
+    __shared__ double redb[kStepWaves][16];
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // which layer and tile
@@ -314,7 +317,7 @@ __global__ __launch_bounds__(64 * kStepWaves) void step_weights_kernel(StepArgs 
     const float* __restrict__ xp = X + (kv ? k0 + r : 0);
     const int groups = (P.B + 3) / 4;
     f32x4_t acc[4] = {};
-    float bs = 0.0f;
+    double bs = 0.0;
     for (int g0 = wave; g0 < groups; g0 += 4 * kStepWaves) {
         float av[4], xv[4];
 #pragma unroll
@@ -328,7 +331,7 @@ __global__ __launch_bounds__(64 * kStepWaves) void step_weights_kernel(StepArgs 
         for (int j = 0; j < 4; ++j) {
             const bool in = 4 * (g0 + j * kStepWaves) + q < P.B;
             const float a = in && ov ? av[j] : 0.0f, x = in && kv ? xv[j] : 0.0f;
-            bs += a;
+            if (k0 == 0) bs += (double)a;
             acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, x, acc[j], 0, 0, 0);
         }
     }
@@ -362,11 +365,11 @@ __global__ __launch_bounds__(64 * kStepWaves) void step_weights_kernel(StepArgs 
     } else if (tid < 272 && k0 == 0) {
         const int o = o0 + tid - 256;
         if (o < O) {
-            float v[kStepWaves];
+            double v[kStepWaves];
 #pragma unroll
             for (int w = 0; w < kStepWaves; ++w) v[w] = redb[w][tid - 256];
-            const float gr = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
-            P.compute[P.layer[l].bl + o] = apply(P.layer[l].mb + o, gr);
+            const double gr = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+            P.compute[P.layer[l].bl + o] = apply(P.layer[l].mb + o, (float)gr);
         }
     }
 }

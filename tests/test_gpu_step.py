@@ -11,8 +11,8 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_helpers import GpuRun, note
-from paper_2606_00946_amd import synth
+from gpu_helpers import GpuRun, note, to_dev
+from paper_2606_00946_amd import lodestar, synth
 from test_gpu_depth import compare_update, mode_of
 
 pytestmark = pytest.mark.gpu
@@ -44,3 +44,29 @@ def test_step_parity(d, hidden, dtype, B):
                         w.inst_feat, w.inst_off, w.inst_hashes)
     assert np.array_equal(scored["scores"], want["scores"].astype(np.float32))
     run.ctx.close()
+
+
+@pytest.mark.parametrize("B", [8192, 8191, 1000])
+def test_bias_gradients_are_summed_in_64_bits(B):
+    """One hidden layer whose units are all on and equal and whose samples are all
+    equal, so that every bias gradient is the sum of B copies of one number; at
+    this target an fp32 sum rounds the same way at every term (64 units in the last
+    place at B = 8,192).  Summed in 64 bits, where 2^13 terms of 24 bits are exact,
+    and rounded once: within one unit."""
+    import torch
+    d, h = 16, 16
+    note(f"bias gradients B={B}")
+    ctx = lodestar.Context(d, (h,), "fp32")
+    bias = np.float32(2.0 ** -30)
+    params = np.concatenate([np.zeros(h * d), np.full(h, bias), np.ones(h), np.zeros(1)]).astype(np.float32)
+    ctx.ls_set_model(params, np.zeros(d, np.float32), np.ones(d, np.float32))
+    y = np.float32(-1.999527)
+    g = np.float32(2) * (np.float32(h * bias) - y) / np.float32(B)     # the step's own operations, each rounded once
+    grad = torch.zeros(params.size, dtype=torch.float32, device="cuda")
+    ctx.ls_update(to_dev(np.zeros((B, d), np.float32)), to_dev(np.full(B, y)), 0.0, None, grad)
+    got = grad.cpu().numpy()
+    want = np.float32(B * np.float64(g))
+    ulp = np.spacing(want)
+    biases = np.append(got[h * d:h * d + h], got[-1])
+    assert np.all(np.abs(biases.astype(np.float64) - np.float64(want)) <= ulp), (biases, want)
+    ctx.close()
