@@ -401,11 +401,27 @@ void launch_rows_of(const StepArgs& P, int width, int sp, hipStream_t s) {
 
 }  // namespace
 
-// The layer-by-layer step wins above: at 64-256-256 bf16 it takes 166 us at B =
-// 8,192, this one 139, and this one's time grows with B.
+// The first models to cross over do so here: three layers of 256 with 256 inputs
+// in bf16, 254 us layer by layer and 253 in two launches at B = 8,192; 64-256-256
+// in bf16 151 and 136; in fp32, and at 128 units, two launches still take less than
+// half there (37-128-128-128: 321 and 88).
 constexpr int kStepMaxBatch = 8192;
 
-bool step_fused(const ModelDims& m, int32_t B) { return B <= kStepMaxBatch && step_width(m) <= kStepWidth; }
+// One narrow hidden layer in bf16 crosses earlier.  From 7,681 samples in
+// multiples of eight its layer-by-layer step stores bf16 and runs on the matrix
+// cores (16 workgroups of 512 samples), and with so few units most of the two-launch
+// step's lanes idle: 16-8 39 us layer by layer and 45 in two launches at 8,192,
+// 64-32 47 and 51, 130-8 53 and 66, 200-32 68 and 75.  Between 65 and 128 inputs
+// the lines meet at 16 units (128-8 52 and 55, 128-32 58 and 56).
+static bool step_layers_win(const ModelDims& m, int32_t B) {
+    const int width = step_width(m);
+    return m.bf16 && m.L == 1 && m.h[0] <= (width > 64 && width <= 128 ? 16 : 32) && B > 7680 && B % 8 == 0 &&
+           m.mfma_chains;
+}
+
+bool step_fused(const ModelDims& m, int32_t B) {
+    return B <= kStepMaxBatch && step_width(m) <= kStepWidth && !step_layers_win(m, B);
+}
 
 int64_t step_workspace_bytes(const ModelDims& m, int32_t B) {
     auto up = [](int64_t n) { return (n + 63) & ~int64_t(63); };

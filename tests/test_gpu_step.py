@@ -24,6 +24,8 @@ CASES = [
     (23, (96, 40), "bf16", [7, 33]),
     (41, (17,), "fp32", [19, 256]),
     (30, (100, 256, 33), "bf16", [5, 300]),
+    (64, (8,), "bf16", [7680, 7687, 7688]),                 # one narrow layer: the last batch of two launches
+    (130, (32,), "bf16", [7680, 8192]),
 ]
 
 
