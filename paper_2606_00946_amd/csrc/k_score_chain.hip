@@ -209,15 +209,15 @@ __global__ __launch_bounds__(H) __attribute__((amdgpu_waves_per_eu(4 / NG))) voi
                              scores);
 }
 
-// The candidate band's rescoring: the pairs list[0 .. *count), persistent
-// workgroups.
-template <bool BF, int H, int NG>
+// The candidate band's rescoring (bf16 models of two layers of 256): the pairs
+// list[0 .. *count), persistent workgroups.
+template <int H, int NG>
 __global__ __launch_bounds__(H) __attribute__((amdgpu_waves_per_eu(4 / NG))) void rescore_chain_mfma_kernel(
     ChainModel M, const float* __restrict__ mu, const float* __restrict__ isig, const float* __restrict__ part_t,
     int32_t R, int32_t N, const int64_t* __restrict__ req_off, const int32_t* __restrict__ prompt_len,
     const int32_t* __restrict__ overlap, int block_tokens, const int64_t* __restrict__ list,
     const uint32_t* __restrict__ count, float* __restrict__ scores) {
-    chain_body<BF, H, NG, true>(M, mu, isig, part_t, R, N, req_off, prompt_len, overlap, block_tokens, list, count, scores);
+    chain_body<true, H, NG, true>(M, mu, isig, part_t, R, N, req_off, prompt_len, overlap, block_tokens, list, count, scores);
 }
 
 // Two layers of up to 128 units: a wave scores 32 pairs by itself, with all of
@@ -351,14 +351,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void sc
                                   nullptr, scores);
 }
 
-// The candidate band's rescoring: the pairs list[0 .. *count), persistent waves.
-template <bool BF, int H1, int H2>
+// The candidate band's rescoring (bf16 models): the pairs list[0 .. *count), persistent waves.
+template <int H1, int H2>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void rescore_wave_mfma_kernel(
     PairModel M, const float* __restrict__ mu, const float* __restrict__ isig, const float* __restrict__ part_t,
     int32_t R, int32_t N, const int64_t* __restrict__ req_off, const int32_t* __restrict__ prompt_len,
     const int32_t* __restrict__ overlap, int block_tokens, const int64_t* __restrict__ list,
     const uint32_t* __restrict__ count, float* __restrict__ scores) {
-    wave_body<BF, H1, H2, true>(M, mu, isig, part_t, R, N, req_off, prompt_len, overlap, block_tokens, list, count,
+    wave_body<true, H1, H2, true>(M, mu, isig, part_t, R, N, req_off, prompt_len, overlap, block_tokens, list, count,
                                  scores);
 }
 
@@ -378,8 +378,11 @@ hipError_t launch_chain(const ChainModel& M, const float* mu, const float* isig,
     if (list) {
         // persistent: as many workgroups as fill every CU with four waves a SIMD and as its LDS holds
         const int fit = (int)((160u << 10) / lds), per_cu = fit < 1024 / H ? fit : 1024 / H;
-        hipLaunchKernelGGL((rescore_chain_mfma_kernel<BF, H, NG>), dim3((uint32_t)(n_cu * per_cu)), dim3(H), lds, s, M, mu,
-                           isig, part_t, R, N, req_off, prompt_len, overlap, block_tokens, list, count, scores);
+        if constexpr (BF && H == 256)
+            hipLaunchKernelGGL((rescore_chain_mfma_kernel<H, NG>), dim3((uint32_t)(n_cu * per_cu)), dim3(H), lds, s, M,
+                               mu, isig, part_t, R, N, req_off, prompt_len, overlap, block_tokens, list, count, scores);
+        else
+            return hipErrorInvalidValue;
     } else {
         hipLaunchKernelGGL((score_chain_mfma_kernel<BF, H, NG>),
                            dim3(chain_groups((int64_t)R * N, NG * kChainPairs, H)), dim3(H), lds, s, M, mu, isig, part_t, R, N, req_off, prompt_len, overlap, block_tokens, scores);
@@ -396,9 +399,11 @@ hipError_t launch_wave(const PairModel& M, const float* mu, const float* isig, c
     if (list) {
         // persistent: as many single-wave workgroups as the LDS lets every CU hold
         const int per_cu = (int)((160u << 10) / lds) < 8 ? (int)((160u << 10) / lds) : 8;
-        hipLaunchKernelGGL((rescore_wave_mfma_kernel<BF, H1, H2>), dim3((uint32_t)(n_cu * per_cu)), dim3(64), lds,
-                           s, M, mu, isig, part_t, R, N, req_off, prompt_len, overlap, block_tokens, list, count,
-                           scores);
+        if constexpr (BF)
+            hipLaunchKernelGGL((rescore_wave_mfma_kernel<H1, H2>), dim3((uint32_t)(n_cu * per_cu)), dim3(64), lds, s, M,
+                               mu, isig, part_t, R, N, req_off, prompt_len, overlap, block_tokens, list, count, scores);
+        else
+            return hipErrorInvalidValue;
     } else {
         hipLaunchKernelGGL((score_wave_mfma_kernel<BF, H1, H2>),
                            dim3(chain_groups((int64_t)R * N, kChainPairs, 64)), dim3(64), lds, s, M, mu, isig, part_t, R, N, req_off, prompt_len, overlap, block_tokens, scores);

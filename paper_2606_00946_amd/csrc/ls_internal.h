@@ -244,9 +244,9 @@ hipError_t launch_score_pairs(const ModelDims& m, const float* compute, const fl
                               const int32_t* prompt_len, const int32_t* overlap, float* scores, hipStream_t s);
 // Canonical scores on the matrix cores (one to three hidden layers of equal
 // width 64, 128 or 256): bit-identical to launch_score_pairs and
-// launch_score_generic.  With list and
-// count (device; both or neither) only the pairs list[0 .. *count) are scored,
-// as launch_rescore does.
+// launch_score_generic.  With list and count (device; both or neither; bf16
+// models of two layers) only the pairs list[0 .. *count) are scored, as
+// launch_rescore does.
 bool chain_mfma_supported(const ModelDims& m);
 // Whether canonical scores come from these kernels, and whether from the
 // layer-by-layer forward (which takes scratch of its own): the sizing of a
@@ -324,10 +324,6 @@ hipError_t launch_gather_rows(const int32_t* code, int32_t n, int d, const float
                               const float* bx, const float* by, float* ox, float* oy, hipStream_t s);
 hipError_t launch_scatter_rows(const int32_t* dst, int32_t n, int d, const float* x, const float* y, float* fx,
                                float* fy, hipStream_t s);
-// Candidates are decided in chunks of admission_chunk(nc): dcp holds
-// chunk x cap distances, dcc chunk x chunk, origin cap slots, row and redo cap,
-// rslots chunk + 1.
-int32_t admission_chunk(int32_t nc);
 // Candidates against the pool: embeddings, decisions, the pool's new rows
 // (k_buffer.hip; pools whose members fit a workgroup's registers in
 // k_admit.hip).
