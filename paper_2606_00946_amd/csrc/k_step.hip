@@ -74,11 +74,11 @@ __device__ __forceinline__ float step_drop(const DropArgs& D, int layer, int64_t
 // rows xs + i * kStepRow (one address across the wave: broadcasts), the weights
 // a group of kStepPre inputs ahead.  What bounds it at small batches is the rate
 // at which a CU takes a wave's addresses, about 16 cycles per load of one word a
-// lane (55 cycles per input with four waves).  Tried and no better there: 32
-// inputs ahead, a ring of 64 ahead that runs on over the stages, immediate row
-// offsets, and the weights through LDS in 64 KB chunks of 16-byte loads (21
-// cycles per input, but 3,000 per chunk to fetch and store it; 22.0 against
-// 24.1 us a step at B = 256, 118 against 83 at 8,192).
+// lane (55 cycles per input with four waves).  Where a thread has one sample the
+// group is 32 inputs, else 16.  Tried and no better: a ring of 64 ahead that runs
+// on over the stages, immediate row offsets, and the weights through LDS in 64 KB
+// chunks of 16-byte loads (21 cycles per input, but 3,000 per chunk to fetch and
+// store it; 118 against 83 us a step at 8,192).
 template <bool QW, int SP, int kStepPre>
 __device__ __forceinline__ void step_chain(float (&acc)[SP], const float* __restrict__ w, int64_t ld, int K,
                                            const float* xs) {
@@ -457,8 +457,8 @@ hipError_t launch_step_fused(const ModelDims& m, float* master, float* compute, 
     const int width = step_width(m);
     const int G = width <= 64 ? 4 : width <= 128 ? 2 : 1;
     // samples per thread: one while the workgroups it makes are about one a CU (24 us at B = 256 of the 3 x 128
-    // model, 26 with two), two up to three a CU (30.5 at B = 1,000; 33 with one, 34 with four), then four (83 at
-    // B = 8,192; 115 with two, 158 with one): each weight read then serves more samples
+    // model, 26 with two, all 16 inputs ahead; 22 now), two up to three a CU (30.5 at B = 1,000; 33 with one, 34
+    // with four), then four (83 at B = 8,192; 115 with two, 158 with one): each weight read then serves more samples
     const int sp = B <= 256 * G ? 1 : B <= 768 * G ? 2 : 4;
     if (m.bf16) launch_rows_of<true>(P, width, sp, s);
     else launch_rows_of<false>(P, width, sp, s);
