@@ -22,7 +22,7 @@ MODELS = [(16, (64,), "fp32"), (16, (64, 64), "fp32"), (32, (128, 128, 128), "fp
 
 @pytest.mark.parametrize("d,hidden,dtype", MODELS)
 def test_scores_bit_for_bit(d, hidden, dtype):
-    for R, N in ((1, 1), (31, 1), (11, 3), (1023, 1), (147, 7)):
+    for R, N in ((1, 1), (31, 1), (11, 3), (1023, 1), (1024, 1), (147, 7)):
         note(f"chain scores d={d} hidden={hidden} {dtype} R={R} N={N}")
         cfg = dataclasses.replace(synth.CONFIGS["tiny"], d=d, hidden=hidden, dtype=dtype, R=R, N=N, update_batch=64,
                                   seed=R + N)

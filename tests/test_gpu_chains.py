@@ -1,12 +1,14 @@
 """The canonical fp32 chains on the matrix cores against the same chains on the
 vector ALUs, bit for bit, through the C ABI.
 
-The chains are the update's forward layers and hidden-layer gradients (Section
-4.3.2), the layer-by-layer scorer of models other than two hidden layers, and
-the canonical scores of two-layer models (Section 4.1: the fp32 workloads, and
-the bf16 model's exact mode). ls_set_chain_kernels(0) runs them as v_mfma_f32_32x32x1_2b_f32
-steps, one input k per instruction, wherever a call's batch fills the device.
-ls_set_chain_kernels(1) keeps them on the vector ALUs. The instruction rounds
+The chains are the layer-by-layer update's forward layers and hidden-layer
+gradients (Section 4.3.2: batches above 8,192 samples), the layer-by-layer
+scorer (one or three hidden layers of widths the fused kernel does not take),
+and the fused canonical scores of one to three equal layers (Section 4.1: the
+fp32 workloads, and the bf16 model's exact mode). ls_set_chain_kernels(0) runs
+them as v_mfma_f32_32x32x1_2b_f32 steps, one input k per instruction, wherever a
+call's batch fills the device. ls_set_chain_kernels(1) keeps them on the vector
+ALUs. The instruction rounds
 each multiply-add once, as fmaf does, and both kernels take the inputs in the
 chain's order, so the loss, every gradient and every updated weight must be
 equal bit for bit. Batches are chosen so that the matrix-core kernel runs:
@@ -70,10 +72,11 @@ UPDATE_CASES = [
     ("homogeneous", 66000, (128, 128, 128), "fp32", None),         # the paper's 3 x 128 model
     ("homogeneous", 66000, (128, 128, 128), "bf16", (0.1, 7)),
     ("homogeneous", 70000, (64,), "bf16", None),                   # half-filled unit tiles
-    ("tiny", None, None, None, None),                              # the five configs at their own batch
-    ("homogeneous", None, None, None, None),
-    ("heterogeneous", None, None, None, None),
-    ("long_context", None, None, None, None),
+    ("tiny", 8193, None, None, None),                              # the smallest layer-by-layer batches
+    ("homogeneous", 8200, None, None, None),
+    ("heterogeneous", 9001, None, None, None),
+    ("long_context", 12289, None, None, None),
+    ("large_batch", 8200, None, None, None),                       # bf16 activations, a ragged split-K chunk
 ]
 
 
@@ -94,12 +97,8 @@ def test_update_chain_kernels_bitwise(base, B, hidden, dtype, dropout):
     assert np.linalg.norm(g - r) <= 1e-4 * np.linalg.norm(r)
 
 
-@pytest.mark.parametrize("hidden,dtype", [((128, 128, 128), "fp32"), ((128, 128, 128), "bf16"), ((64,), "bf16")])
-def test_layer_by_layer_scores_on_matrix_cores(hidden, dtype):
-    """2,100 x 33 pairs: a 65,536-pair chunk on the matrix cores and a ragged
-    3,764-pair chunk on the vector ALUs, every score against the oracle's chain."""
-    w = _workload("homogeneous", hidden=hidden, dtype=dtype, R=2100, N=33)
-    note(f"layer-by-layer scores on the matrix cores hidden={hidden} {dtype}")
+def _scores_in_both_modes(hidden, dtype, R):
+    w = _workload("homogeneous", hidden=hidden, dtype=dtype, R=R, N=33)
     outs = []
     for mode in (0, 1):
         run = GpuRun(w)
@@ -117,6 +116,26 @@ def test_layer_by_layer_scores_on_matrix_cores(hidden, dtype):
     np.testing.assert_array_equal(out["scores"].view(np.uint32), ref["scores"].astype(np.float32).view(np.uint32))
     np.testing.assert_array_equal(out["chosen"], ref["chosen"])
     np.testing.assert_array_equal(out["min_ttft"].view(np.uint32), ref["min_ttft"].astype(np.float32).view(np.uint32))
+
+
+@pytest.mark.parametrize("hidden,dtype,R", [((128, 64, 128), "fp32", 2100), ((96,), "bf16", 2100),
+                                            ((100, 256, 33), "bf16", 2100), ((100, 256, 33), "fp32", 2000),
+                                            ((512, 64, 64), "fp32", 2000)])
+def test_layer_by_layer_scores_on_matrix_cores(hidden, dtype, R):
+    """Widths that the fused kernel does not take.  2,100 x 33 pairs: a
+    65,536-pair chunk on the matrix cores and a ragged one of 3,764; 2,000 x 33
+    leaves 464, which stay on the vector ALUs.  512 units are on the vector ALUs
+    altogether.  Every score against the oracle's chain."""
+    note(f"layer-by-layer scores on the matrix cores hidden={hidden} {dtype} R={R}")
+    _scores_in_both_modes(hidden, dtype, R)
+
+
+@pytest.mark.parametrize("hidden,dtype", [((128, 128, 128), "fp32"), ((128, 128, 128), "bf16"), ((64,), "bf16")])
+def test_fused_scores_equal_layer_by_layer(hidden, dtype):
+    """One and three equal layers: the fused chain kernel (mode 0) against the
+    layer-by-layer forward on the vector ALUs (mode 1) and the oracle."""
+    note(f"fused against layer-by-layer scores hidden={hidden} {dtype}")
+    _scores_in_both_modes(hidden, dtype, 2100)
 
 
 # (config, R, exact mode): the fp32 workloads score canonically; the bf16 model

@@ -141,7 +141,7 @@ def test_dropout_train_round_paper_model():
 
 
 def test_route_paper_model():
-    """The routing policy with the paper's 3 x 128 model (layer-by-layer scores)."""
+    """The routing policy with the paper's 3 x 128 model (scored by the fused chain kernel)."""
     import torch
     w = workload((128, 128, 128), "fp32", R=96)
     cfg = w.cfg

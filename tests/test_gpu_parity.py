@@ -241,9 +241,10 @@ def test_update_parity(name):
     _check_update(w)
 
 
-@pytest.mark.parametrize("B", [77, 1030, 1032])
+@pytest.mark.parametrize("B", [77, 1030, 1032, 8198, 8200])
 def test_update_parity_bf16_ragged_batch(B):
-    """bf16 update at batch sizes that leave a ragged split-K chunk, aligned and not."""
+    """bf16 update at ragged batch sizes, multiples of eight and not: the two-launch
+    step up to 8,192, above it a ragged split-K chunk."""
     w = workload("large_batch")
     note(f"bf16 update ragged B={B}")
     _check_update(w, w.upd_feats[:B], w.upd_ttft[:B])
