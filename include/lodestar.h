@@ -234,15 +234,19 @@ int ls_score_batch_noalloc(ls_ctx* ctx, int32_t R, int32_t N,
 int ls_set_exact_scores(ls_ctx* ctx, int enable);
 
 /*
- * Which kernels run the canonical fp32 chains of ls_update (the forward layers
- * and the hidden layers' backpropagated gradients, Section 4.3.2) and of the
- * layer-by-layer scorer of models other than two hidden layers (Section 4.1).
- * mode 0 (the default): on the matrix cores wherever a call's batch fills the
- * device.  There v_mfma_f32_32x32x1_2b_f32 takes one input k per instruction
- * and rounds each multiply-add once, as fmaf does, so every chain keeps its
- * order and its bits.  mode 1: on the vector ALUs only.  The two give
- * bit-identical results; the switch exists to compare them.  LS_ERR_INVALID
- * for another mode.  Takes effect for later calls.
+ * Which kernels run the canonical fp32 chains of scoring (Section 4.1: one to
+ * three hidden layers of one width, 64, 128 or 256, in one fused kernel, the
+ * candidate band's rescoring included; other models of one or three layers
+ * layer by layer) and of ls_update's layer-by-layer step (Section 4.3.2: the
+ * forward layers and the hidden layers' backpropagated gradients).
+ * mode 0 (the default): on the matrix cores, layer by layer wherever a call's
+ * batch fills the device.  There v_mfma_f32_32x32x1_2b_f32 takes one input k per
+ * instruction and rounds each multiply-add once, as fmaf does, so every chain
+ * keeps its order and its bits.  mode 1: on the vector ALUs only.  The two give
+ * bit-identical results; the switch exists to compare them.  Updates of up to
+ * 8,192 rows at widths up to 256 step in two launches whose chains are on the
+ * vector ALUs in either mode.  LS_ERR_INVALID for another mode.  Takes effect
+ * for later calls.
  */
 int ls_set_chain_kernels(ls_ctx* ctx, int mode);
 

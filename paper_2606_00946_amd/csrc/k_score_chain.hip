@@ -224,7 +224,8 @@ __global__ __launch_bounds__(H) __attribute__((amdgpu_waves_per_eu(4 / NG))) voi
 // layer 2's passes in its accumulators and the head in lanes 0-31, which take
 // units 4-7 of every 8 from lanes 32-63 by a lane shuffle.  No barriers; the tile
 // leaves LDS for two waves per SIMD and the kernels hold their registers to that.
-// (131,072 pairs of h = 128: 62.5 us; a workgroup of two waves 67.6.)
+// (131,072 pairs of h = 128: 62.5 us; a workgroup of two waves 67.6.  Small
+// batches and short lists were not compared.)
 template <bool BF, int H1, int H2, bool LIST>
 __device__ __forceinline__ void wave_body(const PairModel& M, const float* __restrict__ mu,
                                            const float* __restrict__ isig, const float* __restrict__ part_t,
