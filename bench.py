@@ -57,18 +57,19 @@ KIND_KERNELS = {
     "prefix_match": (["ls::group_insert_kernel", "ls::group_lcp_kernel", "ls::cont_scan_kernel",
                       "ls::leaders_first_kernel", "ls::leaders_rest_kernel",
                       "ls::followers_resolve_kernel", "ls::followers_probe_kernel"], ["k_prefix.hip", "ls_internal.h"]),
-    "rescore": (["ls::rescore_chain_mfma_kernel", "ls::rescore_wave_kernel"],
+    "rescore": (["ls::rescore_chain_mfma_kernel", "ls::rescore_wave_mfma_kernel", "ls::rescore_wave_kernel"],
                 ["k_score_chain.hip", "k_band.hip", "k_common.h", "k_policy.h", "ls_internal.h"]),
-    "score_pairs": (["ls::score_chain_mfma_kernel", "ls::score_pairs_kernel"],
+    "score_pairs": (["ls::score_chain_mfma_kernel", "ls::score_wave_mfma_kernel", "ls::score_pairs_kernel"],
                     ["k_score_chain.hip", "k_score.hip", "k_common.h", "ls_internal.h"]),
-    "update": (["ls::normalize_kernel", "ls::normalize_b16_kernel", "ls::dense_mfma_kernel", "ls::dense_lane_kernel", "ls::dense_small_kernel",
+    "update": (["ls::step_rows_kernel", "ls::step_weights_kernel", "ls::normalize_kernel", "ls::normalize_b16_kernel", "ls::dense_mfma_kernel", "ls::dense_lane_kernel", "ls::dense_small_kernel",
                 "ls::layer_fwd_kernel",
                 "ls::loss_grad_kernel", "ls::loss_final_kernel", "ls::wgrad_direct_kernel", "ls::wgrad_row_kernel",
                 "ls::wgrad_reduce_wave_kernel", "ls::wgrad_reduce_kernel", "ls::wgrad_mfma_kernel",
                 "ls::delta_head_kernel", "ls::delta_head_b16_kernel", "ls::backprop_hidden_kernel", "ls::gemm_nt_splitk_kernel",
                 "ls::splitk_reduce_kernel", "ls::rowsum_kernel", "ls::sgd_kernel", "ls::refresh_compute_kernel",
                 "ls::prepare_mfma_kernel"],
-               ["k_update.hip", "k_score.hip", "k_score_mfma.hip", "k_common.h", "k_policy.h", "ls_internal.h"]),
+               ["k_step.hip", "k_update.hip", "k_score.hip", "k_score_mfma.hip", "k_common.h", "k_policy.h",
+                "ls_internal.h"]),
 }
 
 
